@@ -133,7 +133,8 @@ mbl_status mbl_fold_apply(mbl_ham H, double sigma, mbl_precision prec,
 
 /* W = m steps of Jacobi-preconditioned CG on (H - sigma I)^2 W = R, each
  * column independently, starting from W = 0 (the LOBPCG preconditioner,
- * Sec. 3.2).  prec MBL_F64 or MBL_F32 is the element type of R, W and of the
+ * Sec. 3.2).  The kernels are chosen by the sector's size; a launch schedule in
+ * the environment (see mbl_apply_block) selects the row-major gather kernels.  prec MBL_F64 or MBL_F32 is the element type of R, W and of the
  * CG arithmetic.  m >= 0.  Synchronises `stream`. */
 mbl_status mbl_pcg(mbl_ham H, double sigma, mbl_precision prec, const void* R,
                    int64_t ldr, void* W, int64_t ldw, int b, int m,
@@ -249,7 +250,9 @@ typedef struct {
   int64_t cg_apply1_launches[2], cg_apply2_launches[2];  /* [0]=FP64 [1]=FP32 */
   double cg_apply1_ms[2], cg_apply2_ms[2];
   /* algorithmic bytes of those launches: apply1 2nws + 12n, apply2
-     6nws + (12 + s)n for a launch over w columns of s-byte scalars          */
+     6nws + (12 + s)n for a launch over w columns of s-byte scalars; with
+     panel-major CG vectors (sectors of more than 13,312 rows, 14 <= L <= 28)
+     2nws and 3nws: x is updated with p there, and no table of n is read      */
   double cg_apply1_bytes[2], cg_apply2_bytes[2];
   int64_t pcg_columns;   /* CG steps times block columns, summed over inner
                             solves (fewer than pcg_steps * block with lock or

@@ -35,6 +35,7 @@
 #include <memory>
 #include <mutex>
 
+#include "cg_replay.h"
 #include "common.h"
 
 namespace mbl {
@@ -778,6 +779,28 @@ void PcgTiming::init() {
   ready = true;
 }
 
+// Adds the first `ntimed` steps' events and what they stand for: `run` steps of
+// b1 and b2 algorithmic bytes per launch of the two kernels.
+void PcgTiming::collect(int ntimed, int run, double b1, double b2, hipStream_t s) {
+  MBL_HIP(hipStreamSynchronize(s));
+  double t[2] = {0, 0};
+  for (int k = 0; k < ntimed; ++k)
+    for (int i = 0; i < 2; ++i) {
+      float x = 0.f;
+      MBL_HIP(hipEventElapsedTime(&x, ev[4 * k + 2 * i], ev[4 * k + 2 * i + 1]));
+      t[i] += x;
+    }
+  launches_all += run;
+  const double bytes1[2] = {b1, b2};
+  for (int i = 0; i < 2; ++i) {
+    ms[i] += t[i];
+    launches[i] += ntimed;
+    bytes[i] += ntimed * bytes1[i];
+    ms_all[i] += t[i] / ntimed * run;
+    bytes_all[i] += run * bytes1[i];
+  }
+}
+
 PcgTiming::~PcgTiming() {
   if (!ready) return;
   for (auto& e : ev) (void)hipEventDestroy(e);
@@ -800,86 +823,6 @@ int pcg_chunk_width(int64_t n, int b) {
   while (w * 2 <= b && (double)(w * 2) * per_col <= budget) w *= 2;
   if (w < min_w || (double)w * per_col > budget) return b;
   return w;
-}
-
-// Replays `step` m - it times: from a hipGraph captured on a private
-// non-blocking stream (forked from and joined back to s by events) when at
-// least 8 steps remain, else launch by launch.  The legacy default stream
-// cannot be captured, and a capture on a caller's blocking stream would forbid
-// legacy-stream work in every other thread of the process meanwhile.
-// With a stop check the replays are issued in chunks of kStopChunk, one chunk
-// queued ahead of the one running, and no further chunk is issued once the
-// check triggers.  Returns the number of steps run.
-constexpr int kStopChunk = 32;
-
-template <class F>
-int replay_steps(F&& step, int it, int m, hipStream_t& s, const StopCheck* stop) {
-  if (env_int("MBL_PCG_GRAPH", 1) != 0 && m - it >= 8) {
-    hipStream_t own = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr, mark[2] = {nullptr, nullptr};
-    MBL_HIP(hipStreamCreateWithFlags(&own, hipStreamNonBlocking));
-    hipError_t err = hipEventCreateWithFlags(&fork, hipEventDisableTiming);
-    if (err == hipSuccess) err = hipEventCreateWithFlags(&join, hipEventDisableTiming);
-    for (int k = 0; k < 2 && err == hipSuccess; ++k)
-      err = hipEventCreateWithFlags(&mark[k], hipEventDisableTiming);
-    if (err == hipSuccess) err = hipEventRecord(fork, s);
-    if (err == hipSuccess) err = hipStreamWaitEvent(own, fork, 0);
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
-    if (err == hipSuccess) err = hipStreamBeginCapture(own, hipStreamCaptureModeThreadLocal);
-    if (err == hipSuccess) {
-      const hipStream_t keep = s;
-      s = own;  // step() launches on s
-      try {
-        step();
-      } catch (...) {
-        s = keep;
-        hipGraph_t dropped = nullptr;
-        (void)hipStreamEndCapture(own, &dropped);
-        if (dropped) (void)hipGraphDestroy(dropped);
-        (void)hipStreamSynchronize(own);
-        (void)hipStreamDestroy(own);
-        (void)hipEventDestroy(fork);
-        (void)hipEventDestroy(join);
-        for (hipEvent_t e : mark)
-          if (e) (void)hipEventDestroy(e);
-        throw;
-      }
-      s = keep;
-      err = hipStreamEndCapture(own, &graph);
-    }
-    if (err == hipSuccess) err = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    int chunk = 0;
-    while (err == hipSuccess && it < m) {
-      const int end = stop ? std::min(m, it + kStopChunk) : m;
-      for (; err == hipSuccess && it < end; ++it) err = hipGraphLaunch(exec, own);
-      if (!stop || err != hipSuccess || it >= m) continue;
-      // wait for the chunk before this one, then decide whether to go on
-      err = hipEventRecord(mark[chunk & 1], own);
-      if (err == hipSuccess && chunk > 0) err = hipEventSynchronize(mark[(chunk - 1) & 1]);
-      ++chunk;
-      if (err == hipSuccess && stop->triggered()) break;
-    }
-    if (err == hipSuccess) err = hipEventRecord(join, own);
-    if (err == hipSuccess) err = hipStreamWaitEvent(s, join, 0);
-    // the graph and its stream are torn down only after the replays finished
-    const hipError_t se = hipStreamSynchronize(own);
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    (void)hipStreamDestroy(own);
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
-    for (hipEvent_t e : mark)
-      if (e) (void)hipEventDestroy(e);
-    MBL_HIP(err);
-    MBL_HIP(se);
-    return it;
-  }
-  for (; it < m; ++it) {
-    if (stop && it % kStopChunk == 0 && stop->triggered()) break;
-    step();
-  }
-  return it;
 }
 
 // Block PCG of one column chunk through the split (two-pass) kernels:
@@ -932,37 +875,17 @@ void run_pcg_split(const Ham& H, double sigma, const T* jac, const T* Rc, int64_
     MBL_HIP(hipEventRecord(tm->ev[4 * it + 3], s));
     fin(nwp, FB{}, s);
   }
-  auto step = [&]() {
-    const int nwp1 = split_cg_apply<T>(H, sigma, 0, sg, s);
-    fin(nwp1, FA{}, s);
-    const int nwp2 = split_cg_apply<T>(H, sigma, 1, sg, s);
-    fin(nwp2, FB{}, s);
+  auto step = [&](hipStream_t st) {
+    const int nwp1 = split_cg_apply<T>(H, sigma, 0, sg, st);
+    fin(nwp1, FA{}, st);
+    const int nwp2 = split_cg_apply<T>(H, sigma, 1, sg, st);
+    fin(nwp2, FB{}, st);
   };
   const int run = replay_steps(step, it, m, s, stop);
   if (ntimed > 0) {
-    MBL_HIP(hipStreamSynchronize(s));
-    double sa = 0.0, sc = 0.0;
-    for (int k = 0; k < ntimed; ++k) {
-      float ta = 0.f, tc = 0.f;
-      MBL_HIP(hipEventElapsedTime(&ta, tm->ev[4 * k + 0], tm->ev[4 * k + 1]));
-      MBL_HIP(hipEventElapsedTime(&tc, tm->ev[4 * k + 2], tm->ev[4 * k + 3]));
-      sa += ta;
-      sc += tc;
-    }
     // algorithmic bytes: apply1 (p-update fused) reads r, p and writes p, T;
     // apply2 reads T, p, x, r and writes x, r
-    const double b1 = 4.0 * n * w * sizeof(T), b2 = 6.0 * n * w * sizeof(T);
-    tm->ms[0] += sa;
-    tm->ms[1] += sc;
-    tm->launches[0] += ntimed;
-    tm->launches[1] += ntimed;
-    tm->bytes[0] += ntimed * b1;
-    tm->bytes[1] += ntimed * b2;
-    tm->launches_all += run;
-    tm->ms_all[0] += sa / ntimed * run;
-    tm->ms_all[1] += sc / ntimed * run;
-    tm->bytes_all[0] += run * b1;
-    tm->bytes_all[1] += run * b2;
+    tm->collect(ntimed, run, 4.0 * n * w * sizeof(T), 6.0 * n * w * sizeof(T), s);
     tm->split = true;
   }
 }
@@ -994,7 +917,6 @@ struct CgJob {
   T *r, *p, *t;
   double* part;
   PcgCoef* coef;
-  hipStream_t s;
 };
 
 struct CgFuser {
@@ -1151,12 +1073,12 @@ void run_pcg_fused(const std::vector<CgJob<T>*>& g, hipStream_t s) {
     using FB = std::integral_constant<int, FIN_BETA>;
     launch_elt_multi(ei, LI{}, s);
     launch_fin(FI{}, s);
-    auto step = [&]() {
-      launch_apply_multi(m1, E1{}, s);
-      launch_fin(FA{}, s);
-      launch_apply_multi(m2, E2{}, s);
-      launch_fin(FB{}, s);
-      launch_elt_multi(eu, LU{}, s);
+    auto step = [&](hipStream_t st) {
+      launch_apply_multi(m1, E1{}, st);
+      launch_fin(FA{}, st);
+      launch_apply_multi(m2, E2{}, st);
+      launch_fin(FB{}, st);
+      launch_elt_multi(eu, LU{}, st);
     };
     replay_steps(step, 0, m, s, nullptr);
   }
@@ -1179,11 +1101,10 @@ void cg_fuser_stats(const CgFuser* f, int64_t* groups, int64_t* jobs) {
 thread_local CgFuser* t_cg_fuser = nullptr;
 
 // One CG call through the fuser: returns after the call's work (its own or
-// its group's) is enqueued and `job.s` waits for it.
-template <class T>
-void fuse_pcg(CgFuser& f, CgJob<T>& job) {
-  std::vector<int64_t> key = {(int64_t)sizeof(T), job.b, job.m, job.aligned ? 1 : 0,
-                              job.sc.chunk_bytes, job.sc.lane_bytes, job.sc.grp, job.sc.slots};
+// its group's) is enqueued and `s` waits for it.
+// `key`: calls with the same one may share launches; run(jobs): the group's work.
+template <class Job, class Run>
+void fuse_call(CgFuser& f, const std::vector<int64_t>& key, Job& job, hipStream_t s, Run&& run) {
   CgFuser::Ticket tk;
   tk.job = &job;
   MBL_HIP(hipEventCreateWithFlags(&tk.ready, hipEventDisableTiming));
@@ -1195,7 +1116,7 @@ void fuse_pcg(CgFuser& f, CgJob<T>& job) {
       (void)hipEventDestroy(t.finished);
     }
   } ev{tk};
-  MBL_HIP(hipEventRecord(tk.ready, job.s));  // R and the caller's buffers are ready
+  MBL_HIP(hipEventRecord(tk.ready, s));  // R and the caller's buffers are ready
   std::unique_lock<std::mutex> lk(f.mu);
   std::shared_ptr<CgFuser::Group> grp;
   bool leader = false;
@@ -1229,13 +1150,13 @@ void fuse_pcg(CgFuser& f, CgJob<T>& job) {
     lk.unlock();
     std::exception_ptr err;
     try {
-      std::vector<CgJob<T>*> jobs;
+      std::vector<Job*> jobs;
       for (CgFuser::Ticket* t : members) {
-        jobs.push_back(static_cast<CgJob<T>*>(t->job));
-        if (t != &tk) MBL_HIP(hipStreamWaitEvent(job.s, t->ready, 0));
+        jobs.push_back(static_cast<Job*>(t->job));
+        if (t != &tk) MBL_HIP(hipStreamWaitEvent(s, t->ready, 0));
       }
-      run_pcg_fused<T>(jobs, job.s);
-      for (CgFuser::Ticket* t : members) MBL_HIP(hipEventRecord(t->finished, job.s));
+      run(jobs);
+      for (CgFuser::Ticket* t : members) MBL_HIP(hipEventRecord(t->finished, s));
     } catch (...) {
       err = std::current_exception();
     }
@@ -1248,7 +1169,16 @@ void fuse_pcg(CgFuser& f, CgJob<T>& job) {
   }
   lk.unlock();
   if (tk.err) std::rethrow_exception(tk.err);
-  MBL_HIP(hipStreamWaitEvent(job.s, tk.finished, 0));
+  MBL_HIP(hipStreamWaitEvent(s, tk.finished, 0));
+}
+
+// A launch schedule or the two-pass kernels asked for through the environment
+// concern the gather kernels: the CG then runs on those.
+bool gather_forced() {
+  for (const char* v : {"MBL_APPLY_CHUNK_BYTES", "MBL_APPLY_LANE_BYTES", "MBL_APPLY_XCD_GROUP",
+                        "MBL_APPLY_SLOTS_PER_XCD"})
+    if (std::getenv(v)) return true;
+  return env_int("MBL_APPLY_SPLIT", 0) != 0;
 }
 
 template <class T>
@@ -1258,6 +1188,16 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
   const int64_t n = H.n;
   if (n == 0 || b == 0) return;
   const int wc = pcg_chunk_width<T>(n, b);
+  if (wc == b && !gather_forced()) {
+    if (panel_usable(H, b)) {
+      // Panels: measured no slower than the gather kernels at L = 17 to 24 for 1 to
+      // 128 columns of either type (us per step, panels for gathers: L = 17, 64
+      // FP64 columns 57 for 57; L = 18, 32 FP32 41 for 46; L = 20, 64 FP64 217 for 303;
+      // L = 21, 17 FP64 146 for 359; L = 24, 64 FP32 1,880 for 2,580).
+      run_pcg_panel<T>(H, sigma, jac, R, ldr, W, ldw, b, m, s, tm, stop, keep, m_keep);
+      return;
+    }
+  }
   if (t_cg_fuser && wc == b && keep < 0 && tm == nullptr && stop == nullptr && m >= 1) {
     // concurrent solves of a batch: this call may run in one launch with others
     CgJob<T> job{};
@@ -1284,8 +1224,10 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       job.t = tb.as<T>();
       job.part = pa.as<double>();
       job.coef = cb.as<PcgCoef>();
-      job.s = s;
-      fuse_pcg<T>(*t_cg_fuser, job);
+      fuse_call(*t_cg_fuser,
+                {(int64_t)sizeof(T), b, m, job.aligned ? 1 : 0, job.sc.chunk_bytes,
+                 job.sc.lane_bytes, job.sc.grp, job.sc.slots},
+                job, s, [&](const std::vector<CgJob<T>*>& jobs) { run_pcg_fused<T>(jobs, s); });
       return;
     }
   }
@@ -1351,12 +1293,12 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       a2.part = part.as<double>();
       const int ntimed = (tm && timed) ? std::min(to - from, PcgTiming::kSample) : 0;
       if (ntimed) tm->init();
-      auto step = [&]() {
-        dispatch_apply<T, EPI_NORM2>(ch, g, a1, s);
-        finalize<FIN_ALPHA>(ch, g, part.as<double>(), cf, s);
-        dispatch_apply<T, EPI_PCG>(ch, g, a2, s);
-        finalize<FIN_BETA>(ch, g, part.as<double>(), cf, s);
-        dispatch_elt<T, ELT_PUPD>(ch, g, e, s);
+      auto step = [&](hipStream_t st) {
+        dispatch_apply<T, EPI_NORM2>(ch, g, a1, st);
+        finalize<FIN_ALPHA>(ch, g, part.as<double>(), cf, st);
+        dispatch_apply<T, EPI_PCG>(ch, g, a2, st);
+        finalize<FIN_BETA>(ch, g, part.as<double>(), cf, st);
+        dispatch_elt<T, ELT_PUPD>(ch, g, e, st);
       };
       int it = from;
       for (int k = 0; k < ntimed; ++k, ++it) {
@@ -1374,28 +1316,8 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       // lives on the device, so the five launches are identical each step.
       const int run = replay_steps(step, it, to, s, stop) - from;
       if (ntimed > 0) {
-        MBL_HIP(hipStreamSynchronize(s));
-        double sa = 0.0, sc = 0.0;
-        for (int k = 0; k < ntimed; ++k) {
-          float ta = 0.f, tc = 0.f;
-          MBL_HIP(hipEventElapsedTime(&ta, tm->ev[4 * k + 0], tm->ev[4 * k + 1]));
-          MBL_HIP(hipEventElapsedTime(&tc, tm->ev[4 * k + 2], tm->ev[4 * k + 3]));
-          sa += ta;
-          sc += tc;
-        }
-        const double b1 = 2.0 * n * ch.w * sizeof(T) + 12.0 * n;
-        const double b2 = 6.0 * n * ch.w * sizeof(T) + (12.0 + sizeof(T)) * n;
-        tm->ms[0] += sa;
-        tm->ms[1] += sc;
-        tm->launches[0] += ntimed;
-        tm->launches[1] += ntimed;
-        tm->bytes[0] += ntimed * b1;
-        tm->bytes[1] += ntimed * b2;
-        tm->launches_all += run;
-        tm->ms_all[0] += sa / ntimed * run;
-        tm->ms_all[1] += sc / ntimed * run;
-        tm->bytes_all[0] += run * b1;
-        tm->bytes_all[1] += run * b2;
+        tm->collect(ntimed, run, 2.0 * n * ch.w * sizeof(T) + 12.0 * n,
+                    6.0 * n * ch.w * sizeof(T) + (12.0 + sizeof(T)) * n, s);
       }
     };
     for (const Chunk& ch : plan_chunks<T>(w, aligned, sc)) {

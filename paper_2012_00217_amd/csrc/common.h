@@ -139,6 +139,28 @@ struct SplitTables {
   DevBuf Elo_v, Ehi_v;           // double by value (for the diagonal kernel)
 };
 
+// One tile of the panel CG (cg_panel.hip): the block of rows that share the high
+// configuration hi (the sites from q = 12 up).
+struct PanelTile {
+  int32_t row0, nrows;      // first row, rows
+  int32_t aux;              // first of its low configurations in lo_tab / lo_E
+  int32_t nd;               // anti-aligned bonds inside hi
+  int32_t mlo, mhi, mbase;  // middle bond: rows [mlo, mhi) map to rows mbase + u
+  int32_t cnt;              // anti-aligned bonds of hi: row u maps to row0 + off + u
+  double E;                 // energy of hi
+  int32_t off[16];
+};
+
+// Tables of the panel CG, built once per sector.
+struct PanelTables {
+  bool ok = false;
+  int ntiles = 0;
+  DevBuf buf;                // holds the three tables below
+  PanelTile* tiles = nullptr;  // by high configuration, which is row order
+  uint4* lo_tab = nullptr;     // per low configuration (k_panel_tables)
+  double* lo_E = nullptr;
+};
+
 // Per-sector Hamiltonian data (the opaque mbl_ham).
 struct Ham {
   int L = 0, nup = 0;
@@ -151,6 +173,7 @@ struct Ham {
   DevBuf diag;     // double [n]  <s|H|s>
   std::vector<uint32_t> pascal_host;
   SplitTables split;
+  PanelTables panel;
   // Stream the tables are allocated and freed on, stream-ordered (worker
   // solves of the batch and the server), or nullptr: hipMalloc / hipFree
   // after a device synchronisation (handles of the C ABI).
@@ -235,6 +258,7 @@ struct PcgTiming {
   double bytes_all[2] = {0, 0};
   bool split = false;        // the timed steps ran the two-pass kernels
   void init();
+  void collect(int ntimed, int run, double b1, double b2, hipStream_t s);
   ~PcgTiming();
 };
 
@@ -289,6 +313,15 @@ template <class T>
 void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W, int64_t ldw,
              int b, int m, hipStream_t s, PcgTiming* tm = nullptr,
              const StopCheck* stop = nullptr, int keep = -1, int m_keep = 0);
+
+// The same with panel-major CG vectors (cg_panel.hip), for sectors whose vectors
+// leave the caches; panel_usable: the sector has its tables.
+void build_panel_tables(Ham& H, hipStream_t s);
+bool panel_usable(const Ham& H, int b);
+template <class T>
+void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W,
+                   int64_t ldw, int b, int m, hipStream_t s, PcgTiming* tm, const StopCheck* stop,
+                   int keep, int m_keep);
 
 // Fused CG of concurrent solves (the batch): while a thread's t_cg_fuser is
 // set, its run_pcg calls without a stop check, timing or guard columns join

@@ -1,0 +1,80 @@
+"""The CG paths behind mbl_pcg at the sizes where each can go wrong, against the
+oracle's step-by-step PCG: panel-major vectors (ragged panels, unaligned blocks,
+S^z != 0, frozen guard columns, the largest chains).
+
+Tolerances: m <= 9 CG steps amplify rounding by less than 1e4 (FP64 to 1e-9 of the
+largest entry; FP32 to 2e-4 of the column norm).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import basis, hamiltonian, linalg, pcg as opcg
+from paper_2012_00217_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+api = pytest.importorskip("paper_2012_00217_amd.api")
+DEV = "cuda"
+
+
+def _check(L, Sz, b, dtype, m, J=1.0, Delta=1.0, pad=0, offset=0):
+    h = workloads.disorder(L, 4.0, 3)
+    H = api.Hamiltonian(L, h, Sz=Sz, J=J, Delta=Delta)
+    _, Ho = hamiltonian.sector_matrix(L, basis.nup_from_sz(L, Sz), J, Delta, h)
+    sigma = 0.13
+    R = workloads.random_block(H.n, b, seed=L + b)
+    big = torch.zeros((H.n, b + pad), dtype=dtype, device=DEV)
+    Rd = big[:, offset:offset + b]
+    Rd.copy_(torch.from_numpy(R).to(DEV, dtype))
+    W = H.pcg(Rd, sigma, m).double().cpu().numpy()
+    Wr = opcg.pcg_fold(Ho, sigma, hamiltonian.fold_diagonal(Ho, sigma),
+                       Rd.double().cpu().numpy(), m)
+    if dtype == torch.float64:
+        np.testing.assert_allclose(W, Wr, rtol=0, atol=1e-9 * max(1e-300, np.abs(Wr).max()))
+    else:
+        err = np.linalg.norm(W - Wr, axis=0)
+        assert np.all(err <= 2e-4 * np.linalg.norm(Wr, axis=0))
+
+
+# n = 12376 (L = 17, S^z = 3.5; a sector the column path takes), 19448, 18564,
+# 24310, 48620; m = 9 replays a captured step
+@pytest.mark.parametrize("L,Sz,J,Delta", [(17, 1.5, 0.7, -1.3), (18, 3.0, 1.0, 1.0),
+                                          (17, -0.5, 1.0, 0.0), (18, 0.0, 1.3, 0.6)])
+@pytest.mark.parametrize("dtype,b,m,pad,offset", [
+    (torch.float64, 1, 9, 0, 0), (torch.float64, 2, 1, 0, 0), (torch.float64, 17, 3, 4, 1),
+    (torch.float64, 34, 2, 2, 0), (torch.float32, 1, 3, 0, 0), (torch.float32, 3, 9, 5, 2),
+    (torch.float32, 66, 3, 6, 4), (torch.float32, 64, 0, 0, 0)])
+def test_panel_cg(L, Sz, J, Delta, dtype, b, m, pad, offset):
+    _check(L, Sz, b, dtype, m, J, Delta, pad, offset)
+
+
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+def test_panel_cg_guard_columns(precision):
+    """Columns beyond nev stop early, with nev not a whole number of panels."""
+    L = 17
+    h = workloads.disorder(L, 6.0, 2)
+    H = api.Hamiltonian(L, h, Sz=0.5)
+    _, Ho = hamiltonian.sector_matrix(L, basis.nup_from_sz(L, 0.5), 1.0, 1.0, h)
+    ev, V, rs, info = H.solve(0.1, 5, 12, tol=1e-9, guard_cg=0.3, precision=precision)
+    assert info["pcg_columns"] < 12 * info["pcg_steps"]
+    assert linalg.residual_norms(Ho, ev, V.cpu().numpy()).max() <= 1e-9
+
+
+@pytest.mark.parametrize("L,b,dtype", [(26, 6, torch.float32), (28, 3, torch.float64)])
+def test_panel_cg_at_the_longest_chains(L, b, dtype, monkeypatch):
+    """The panel CG against the row-major gather kernels (oracle-checked at full
+    size elsewhere), which a launch schedule in the environment selects."""
+    h = workloads.disorder(L, 4.0, 0)
+    H = api.Hamiltonian(L, h)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    R = torch.randn(H.n, b, dtype=dtype, device=DEV, generator=g)
+    W = H.pcg(R, 0.2, 2)
+    monkeypatch.setenv("MBL_APPLY_XCD_GROUP", "64")
+    W0 = H.pcg(R, 0.2, 2)
+    err = (W - W0).norm(dim=0) / W0.norm(dim=0)
+    assert err.max().item() <= (1e-12 if dtype == torch.float64 else 2e-5)
+    del W, W0, R
+    torch.cuda.empty_cache()
