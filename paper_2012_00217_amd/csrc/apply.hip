@@ -1189,6 +1189,24 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
   if (n == 0 || b == 0) return;
   const int wc = pcg_chunk_width<T>(n, b);
   if (wc == b && !gather_forced()) {
+    if (H.col_ok) {
+      // One workgroup per column: every sector whose vector fits the LDS.  Per CG
+      // step, against the best of the other two: 3.3 for 24 us (L = 12, 16 FP64
+      // columns), 5.7 for 28 (L = 14, 32 FP64), 14.8 for 30 (L = 16, 32 FP32); 32 for 33
+      // at its largest (L = 16, 32 FP64), where it takes 32 of the 256 CUs.
+      ColumnJob<T> job{&H, sigma, jac, R, ldr, W, ldw, b, m, keep, m_keep};
+      if (t_cg_fuser && keep < 0 && tm == nullptr && stop == nullptr) {
+        fuse_call(*t_cg_fuser, {-(int64_t)sizeof(T), b, m, n}, job, s,
+                  [&](const std::vector<ColumnJob<T>*>& jobs) {
+                    std::vector<ColumnJob<T>> all;
+                    for (const ColumnJob<T>* q : jobs) all.push_back(*q);
+                    run_pcg_column<T>(all, s, nullptr, nullptr);
+                  });
+      } else {
+        run_pcg_column<T>({job}, s, tm, stop);
+      }
+      return;
+    }
     if (panel_usable(H, b)) {
       // Panels: measured no slower than the gather kernels at L = 17 to 24 for 1 to
       // 128 columns of either type (us per step, panels for gathers: L = 17, 64

@@ -174,6 +174,8 @@ struct Ham {
   std::vector<uint32_t> pascal_host;
   SplitTables split;
   PanelTables panel;
+  bool col_ok = false;  // the sector fits the one-workgroup-per-column CG
+  DevBuf col_tab;       // its neighbour lists (cg_column.hip)
   // Stream the tables are allocated and freed on, stream-ordered (worker
   // solves of the batch and the server), or nullptr: hipMalloc / hipFree
   // after a device synchronisation (handles of the C ABI).
@@ -322,6 +324,24 @@ template <class T>
 void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W,
                    int64_t ldw, int b, int m, hipStream_t s, PcgTiming* tm, const StopCheck* stop,
                    int keep, int m_keep);
+
+// The same with one workgroup per column (cg_column.hip), for sectors whose vectors
+// fit the LDS of a CU.
+template <class T>
+struct ColumnJob {
+  const Ham* H;
+  double sigma;
+  const T* jac;
+  const T* R;
+  int64_t ldr;
+  T* W;
+  int64_t ldw;
+  int b, m, keep, m_keep;
+};
+void build_column_tables(Ham& H, hipStream_t s);
+template <class T>
+void run_pcg_column(const std::vector<ColumnJob<T>>& jobs, hipStream_t s, PcgTiming* tm,
+                    const StopCheck* stop);
 
 // Fused CG of concurrent solves (the batch): while a thread's t_cg_fuser is
 // set, its run_pcg calls without a stop check, timing or guard columns join

@@ -125,7 +125,8 @@ void build_tables(Ham& H, hipStream_t s) {
   hipLaunchKernelGGL(k_diag, dim3(grid1(H.n)), dim3(256), 0, s, H.states.as<uint32_t>(), H.n, a,
                      H.diag.as<double>());
   MBL_CHECK_LAUNCH();
-  build_panel_tables(H, s);
+  build_column_tables(H, s);
+  if (!H.col_ok) build_panel_tables(H, s);
 }
 
 void rank_states(const Ham& H, const uint64_t* q_dev, int64_t cnt, int64_t* out_dev,

@@ -1,6 +1,8 @@
 """The CG paths behind mbl_pcg at the sizes where each can go wrong, against the
-oracle's step-by-step PCG: panel-major vectors (ragged panels, unaligned blocks,
-S^z != 0, frozen guard columns, the largest chains).
+oracle's step-by-step PCG: one workgroup per column (sectors whose vector fits the
+LDS: every rows-per-thread variant, its remainders, restarts between launches) and
+panel-major vectors (sectors above: ragged panels, unaligned blocks, S^z != 0,
+frozen guard columns, the largest chains).
 
 Tolerances: m <= 9 CG steps amplify rounding by less than 1e4 (FP64 to 1e-9 of the
 largest entry; FP32 to 2e-4 of the column norm).
@@ -36,6 +38,30 @@ def _check(L, Sz, b, dtype, m, J=1.0, Delta=1.0, pad=0, offset=0):
     else:
         err = np.linalg.norm(W - Wr, axis=0)
         assert np.all(err <= 2e-4 * np.linalg.norm(Wr, axis=0))
+
+
+# n = 2, 3, 10, 70, 924 (one row per thread), 1716 (2), 3432 (4), 5005 and 6435 (7),
+# 8008 and 12870 (13); few up spins on a long chain (2024, 1)
+@pytest.mark.parametrize("L,Sz", [(2, 0.0), (3, 0.5), (5, -0.5), (8, 0.0), (12, 0.0), (13, 0.5),
+                                  (14, 0.0), (15, 1.5), (15, 0.5), (16, 2.0), (16, 0.0), (24, 9.0), (20, 10.0)])
+@pytest.mark.parametrize("dtype,b,m", [(torch.float64, 1, 3), (torch.float64, 5, 1),
+                                       (torch.float32, 3, 3), (torch.float32, 16, 0)])
+def test_column_cg(L, Sz, dtype, b, m):
+    _check(L, Sz, b, dtype, min(m, 2) if L < 5 else m)
+
+
+@pytest.mark.parametrize("L,precision", [(12, "f64"), (13, "pcg32"), (14, "f64"), (15, "f64"),
+                                         (16, "f64"), (16, "mixed")])
+def test_column_cg_restarts_are_bitwise_one_launch(L, precision):
+    """A solve with a time limit stops its CG every 32 steps to look at the clock
+    and goes on from the saved state: the same bits as without."""
+    h = workloads.disorder(L, 6.0, 1)
+    H = api.Hamiltonian(L, h, Sz=0.5 * (L % 2))
+    kw = dict(nev=4, block=8, tol=1e-8, precision=precision, pcg_iters=75, guard_cg=0.5, max_iter=3,
+              raise_on_noconv=False)
+    ev, V, rs, info = H.solve(0.1, **kw)
+    ev2, V2, rs2, info2 = H.solve(0.1, max_seconds=600.0, **kw)
+    assert np.array_equal(ev, ev2) and torch.equal(V, V2) and np.array_equal(rs, rs2)
 
 
 # n = 12376 (L = 17, S^z = 3.5; a sector the column path takes), 19448, 18564,
