@@ -387,9 +387,18 @@ void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, 
 
 // Small dense (single workgroup) FP64 kernels; matrices row-major.
 // small_eigh: ascending eigenvalues w and eigenvectors V (columns) of the
-// symmetric A; V == nullptr asks for eigenvalues only (m <= 128).
+// symmetric A; V == nullptr asks for eigenvalues only (m <= 192).
 void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64_t ldv,
                 double* work, hipStream_t s);
+
+// Eigenvalues of `count` matrices (dim <= max_dim <= 192, row-major, at A + a_at) in one
+// launch, ascending at w + w_at.
+struct EighItem {
+  int dim;
+  int64_t a_at, w_at;
+};
+void eigh_values(int count, int max_dim, const double* A, const EighItem* items_dev, double* w,
+                 hipStream_t s);
 
 // Workspace bytes needed by small_eigh for size m.
 size_t small_eigh_work_bytes(int m);

@@ -5,9 +5,8 @@
 //    round-robin (tournament) pair ordering: in each round the indices are
 //    split into disjoint pairs, so all rotations of a round commute and the
 //    matrix splits into 2 x 2 blocks that are updated independently,
-//    A_kl <- J_k^T A_kl J_l.  Sizes <= 96 run in one workgroup with A and V in
-//    LDS (<= 128 when only eigenvalues are wanted, with A alone in LDS); larger
-//    ones run one kernel per round, ping-ponging A between two
+//    A_kl <- J_k^T A_kl J_l.  Sizes <= 192 run in one workgroup with the upper
+//    triangle of A in LDS; larger ones run one kernel per round, ping-ponging A between two
 //    buffers so the rotations of a round are computed from the unmodified
 //    matrix.  A sweep ends with a count of rotations; none means converged.
 //    Jacobi keeps small eigenvalues of positive semi-definite matrices to
@@ -18,6 +17,7 @@
 //  * Small matrix products and the nearest-shift selection.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 
@@ -26,32 +26,62 @@ namespace {
 
 constexpr double kRotTol = 1e-15;  // rotate when |a_pq| > tol * sqrt(|a_pp a_qq|)
 
-__device__ inline void pair_of(int mm, int round, int k, int* p, int* q) {
+// Pair k of a round: the fixed index mm - 1 (k = 0) or (round + k) mod (mm - 1), and
+// (round - k) mod (mm - 1).  Both move on by one each round.
+struct Pair {
   int a, b;
-  if (k == 0) {
-    a = mm - 1;
-    b = round;
-  } else {
-    a = (round + k) % (mm - 1);
-    b = (round - k + mm - 1) % (mm - 1);
+  bool fixed;  // a stays
+  __device__ Pair() {}
+  __device__ Pair(int mm, int round, int k) : fixed(k == 0) {
+    a = round + k;
+    b = round - k;
+    if (a >= mm - 1) a -= mm - 1;
+    if (b < 0) b += mm - 1;
+    if (fixed) a = mm - 1;
   }
-  *p = min(a, b);
-  *q = max(a, b);
+  __device__ void step(int mm) {
+    const int a1 = a + 1 == mm - 1 ? 0 : a + 1;
+    a = fixed ? a : a1;
+    b = b + 1 == mm - 1 ? 0 : b + 1;
+  }
+};
+
+__device__ inline void pair_of(int mm, int round, int k, int* p, int* q) {
+  const Pair t(mm, round, k);
+  *p = min(t.a, t.b);
+  *q = max(t.a, t.b);
+}
+
+// 1 / sqrt(x) to about an ulp for normal x > 0: the hardware estimate (half the
+// bits) and one third-order correction.
+__device__ inline double rsqrt_fast(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 // Rotation (c, s) that annihilates a_pq:  A' = J^T A J with J_pp = J_qq = c,
 // J_pq = s, J_qp = -s.  Returns false (c = 1, s = 0) when a_pq is negligible.
-__device__ inline bool rotation(double app, double aqq, double apq, double* c, double* s) {
-  if (apq == 0.0 || fabs(apq) <= kRotTol * sqrt(fabs(app * aqq))) {
-    *c = 1.0;
-    *s = 0.0;
-    return false;
-  }
-  const double tau = (aqq - app) / (2.0 * apq);
-  const double t = (tau >= 0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-  *c = 1.0 / sqrt(1.0 + t * t);
-  *s = t * (*c);
-  return true;
+// p > q (swapped) gives the same rotation of the two rows as p < q.
+// With d = a_qq - a_pp, b = 2 a_pq, u = |d| + hypot(d, b) (no cancellation):
+// (c, s) = (u, +-b) / hypot(u, b).  Two reciprocal roots follow each other (d and b are
+// first scaled by a power of two), where tan = 1 / (tau + sqrt(1 + tau^2)),
+// c = 1 / sqrt(1 + tan^2) chains two roots and three divisions; every round of the
+// sweep waits for this.
+__device__ inline bool rotation(double app, double aqq, double apq, bool swapped, double* c,
+                                double* s) {
+  const bool rot = apq != 0.0 && !(fabs(apq) <= kRotTol * sqrt(fabs(app * aqq)));
+  double d = aqq - app, b = 2.0 * apq;
+  const int e = -__builtin_amdgcn_frexp_exp(fmax(fabs(d), fabs(b)));
+  d = ldexp(d, e);
+  b = ldexp(b, e);
+  const double x = fma(d, d, b * b);
+  const double u = fma(x, rsqrt_fast(x), fabs(d));
+  const double q = rsqrt_fast(fma(u, u, b * b));
+  const bool up = d > 0.0 || (d == 0.0 && !swapped);
+  *c = rot ? u * q : 1.0;
+  *s = rot ? (up ? b : -b) * q : 0.0;
+  return rot;
 }
 
 // 2 x 2 block update B' = J_k^T B J_l.
@@ -65,98 +95,369 @@ __device__ inline void rot_block(double ck, double sk, double cl, double sl, dou
   bqq = sl * rqp + cl * rqq;
 }
 
-// Whole Jacobi eigensolver in one workgroup (mm even): A and V in LDS for
-// mm <= 96, or A alone when only eigenvalues are wanted (kVec false, mm <= 128).
-// The pairs of a round are tabulated once per round, and every thread keeps a
-// fixed pair column l (and walks rows k, or matrix rows i, with a fixed stride),
-// so the inner loops do no integer division.
-constexpr int kLdsPairs = 64;  // pairs per round, mm / 2 <= 64
-template <bool kVec>
-__global__ __launch_bounds__(1024) void k_jacobi_lds(int m, const double* __restrict__ A,
-                                                     int64_t lda, double* __restrict__ w,
-                                                     double* __restrict__ V, int64_t ldv,
-                                                     int max_sweeps) {
-  extern __shared__ double sh[];
-  const int mm = m + (m & 1);
-  double* a = sh;             // mm x mm
-  double* v = sh + mm * mm;   // mm x mm (kVec only)
-  __shared__ double cs_c[kLdsPairs], cs_s[kLdsPairs];
-  __shared__ int pp[kLdsPairs], qq[kLdsPairs];
-  __shared__ int nrot;
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int e = tid; e < mm * mm; e += nt) {
-    const int i = e / mm, j = e % mm;
-    a[e] = (i < m && j < m) ? A[(int64_t)i * lda + j] : 0.0;
-    if constexpr (kVec) v[e] = (i == j) ? 1.0 : 0.0;
-  }
-  // symmetrise from the upper triangle
-  __syncthreads();
-  for (int e = tid; e < mm * mm; e += nt) {
-    const int i = e / mm, j = e % mm;
-    if (i > j) a[e] = a[j * mm + i];
-  }
-  __syncthreads();
+// Whole Jacobi eigensolver in one workgroup (mm <= 192, even), A in LDS.  Only the
+// blocks k <= l of a round are worked out, and every thread keeps its blocks
+// through the whole run.  What a round costs is latency (the rotation of its pairs,
+// then the update of the blocks, a barrier after each), so the eigenvectors are
+// kept out of it: they need the rotations alone, row by row independently, and
+// larger sizes record them (kVecRecord) for k_jacobi_vectors to apply on other CUs;
+// sizes up to 48 update V in LDS beside A (kVecInline), which costs less than a second launch.
+enum { kVecNone = 0, kVecInline = 1, kVecRecord = 2 };
+constexpr int kMaxSweeps = 30;
+constexpr int kLdsMax = 192;     // largest size in one workgroup
+constexpr int kSquareMax = 136;  // largest size stored as a full square
+constexpr int kInlineMax = 48;   // largest size with V beside A
+constexpr int kVRows = 4;        // rows of V per thread with V beside A
+
+// Wavefronts by what they do: rotations first, then blocks, then V (kVecInline).
+struct JacobiWaves {
+  int rot, blocks, vec;
+  int threads() const { return 64 * (rot + blocks + vec); }
+};
+inline int jacobi_blocks(int mm) { return (mm / 2) * (mm / 2 + 1) / 2; }
+inline JacobiWaves jacobi_waves(int mm, bool vec) {
+  JacobiWaves w;
   const int np = mm / 2;
-  const int rows_per_pass = nt / np;          // threads sharing one pair column
-  const int l = tid % np, r0 = tid / np;      // this thread's column and first row
-  const bool worker = r0 < rows_per_pass;     // the last nt % np threads idle
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    if (tid == 0) nrot = 0;
-    __syncthreads();
-    for (int round = 0; round < mm - 1; ++round) {
-      if (tid < np) {
-        int p, q;
-        pair_of(mm, round, tid, &p, &q);
-        double c, s;
-        if (rotation(a[p * mm + p], a[q * mm + q], a[p * mm + q], &c, &s)) atomicAdd(&nrot, 1);
-        cs_c[tid] = c;
-        cs_s[tid] = s;
-        pp[tid] = p;
-        qq[tid] = q;
-      }
-      __syncthreads();
-      if (worker) {
-        const int pl = pp[l], ql = qq[l];
-        const double cl = cs_c[l], sl = cs_s[l];
-        for (int k = r0; k < np; k += rows_per_pass) {
-          const int pk = pp[k], qk = qq[k];
-          double bpp = a[pk * mm + pl], bpq = a[pk * mm + ql], bqp = a[qk * mm + pl],
-                 bqq = a[qk * mm + ql];
-          rot_block(cs_c[k], cs_s[k], cl, sl, bpp, bpq, bqp, bqq);
-          if (k == l) {
-            bpq = 0.0;
-            bqp = 0.0;
-          }
-          a[pk * mm + pl] = bpp;
-          a[pk * mm + ql] = bpq;
-          a[qk * mm + pl] = bqp;
-          a[qk * mm + ql] = bqq;
-        }
-        if constexpr (kVec) {
-          for (int i = r0; i < mm; i += rows_per_pass) {
-            const double vp = v[i * mm + pl], vq = v[i * mm + ql];
-            v[i * mm + pl] = cl * vp - sl * vq;
-            v[i * mm + ql] = sl * vp + cl * vq;
-          }
-        }
-      }
-      __syncthreads();
-    }
-    const bool done = (nrot == 0);
-    __syncthreads();
-    if (done) break;
-  }
-  // ascending order (ties by index); padded index mm-1 (if any) is skipped
-  for (int j = tid; j < m; j += nt) {
-    const double dj = a[j * mm + j];
+  if (mm > kSquareMax) return {0, 16, 0};
+  w.rot = (np + 63) / 64;
+  w.vec = vec ? (np * ((mm + kVRows - 1) / kVRows) + 63) / 64 : 0;
+  w.blocks = std::min(16 - w.rot - w.vec, (jacobi_blocks(mm) + 63) / 64);
+  return w;
+}
+inline size_t jacobi_lds_bytes(int mm, bool vec) {
+  const size_t a = mm <= kSquareMax ? mm * (mm + 1) : mm * (mm + 1) / 2;
+  return (a + (vec ? mm * mm : 0)) * sizeof(double) +
+         (size_t)(mm / 2) * (sizeof(double2) + (mm <= kSquareMax ? 0 : sizeof(int4)));
+}
+
+struct JacobiOut {
+  double* w;
+  double* V;      // kVecInline
+  int64_t ldv;
+  double2* rec;   // kVecRecord: (c, s) of every pair of every round
+  int* info;      // kVecRecord: rounds recorded, then the place of every column
+};
+
+// Block e of the list (0,0), (0,1), ..., (0,np-1), (1,1), ...: neighbouring threads
+// read neighbouring columns of one row.
+__device__ inline void block_of(int e, int np, int* k, int* l) {
+  const int nb = np * (np + 1) / 2, g = nb - 1 - min(e, nb - 1);
+  int r = (int)((sqrtf(8.0f * (float)g + 1.0f) - 1.0f) * 0.5f);
+  while (r * (r + 1) / 2 > g) --r;
+  while ((r + 1) * (r + 2) / 2 <= g) ++r;
+  *k = np - 1 - r;
+  *l = np - 1 - (g - r * (r + 1) / 2);
+}
+
+// Eigenvalues (diag(i)) in ascending order (ties by index), and where each went.
+template <int VEC, class F>
+__device__ __forceinline__ void jacobi_sorted(int m, const JacobiOut& o, F&& diag,
+                                              const double* v, int mm) {
+  for (int j = threadIdx.x; j < m; j += blockDim.x) {
+    const double dj = diag(j);
     int r = 0;
     for (int i = 0; i < m; ++i) {
-      const double di = a[i * mm + i];
+      const double di = diag(i);
       r += (di < dj) || (di == dj && i < j);
     }
-    w[r] = dj;
-    if constexpr (kVec)
-      for (int i = 0; i < m; ++i) V[(int64_t)i * ldv + r] = v[i * mm + j];
+    o.w[r] = dj;
+    if constexpr (VEC == kVecRecord) o.info[1 + j] = r;
+    if constexpr (VEC == kVecInline)
+      for (int i = 0; i < m; ++i) o.V[(int64_t)i * o.ldv + r] = v[i * mm + j];
+  }
+}
+
+// mm <= 136: A as a full square of odd stride; blocks k <= l are read once and
+// written to both sides.  NB: blocks per thread.  A wavefront issues one instruction in
+// about five cycles, so the rotations, the blocks and V have wavefronts of their own:
+// while the first ones work out the rotations of a round the others read what they
+// will update; barrier; update; barrier.  The indices of a pair move on by one each
+// round.
+template <int VEC, int NB>
+__device__ __forceinline__ void jacobi_square(int m, const double* __restrict__ A, int64_t lda,
+                                              const JacobiOut& o, const JacobiWaves& jw) {
+  extern __shared__ __align__(16) double sh[];
+  __shared__ int rotated[2];
+  const int mm = m + (m & 1), np = mm / 2, S = mm + 1;
+  double2* cs = reinterpret_cast<double2*>(sh);   // rotation of each pair
+  double* a = reinterpret_cast<double*>(cs + np);
+  double* v = a + mm * S;                         // kVecInline: mm x mm
+  const int tid = threadIdx.x, nt = blockDim.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int e = tid; e < mm * mm; e += nt) {
+    const int i = e / mm, j = e - i * mm;
+    const int r = min(i, j), c = max(i, j);  // symmetrised from the upper triangle
+    a[i * S + j] = c < m ? A[(int64_t)r * lda + c] : 0.0;
+    if constexpr (VEC == kVecInline) v[e] = (i == j) ? 1.0 : 0.0;
+  }
+  if (tid < 2) rotated[tid] = 0;
+  __syncthreads();
+  int sweep = 0;
+  // runs sweeps until one does nothing: per round before(), barrier, after(), barrier
+  auto sweeps = [&](auto&& begin, auto&& before, auto&& after) {
+    for (; sweep < kMaxSweeps; ++sweep) {
+      begin();
+      for (int round = 0; round < mm - 1; ++round) {
+        before();
+        __syncthreads();
+        after();
+        __syncthreads();
+      }
+      const bool more = rotated[sweep & 1] != 0;
+      if (tid == 0) rotated[1 - (sweep & 1)] = 0;
+      __syncthreads();
+      if (!more) break;
+    }
+  };
+  if (wave < jw.rot) {
+    Pair mine;
+    double2* rec = o.rec + tid;
+    const bool act = tid < np;
+    sweeps([&] { mine = Pair(mm, 0, min(tid, np - 1)); },
+           [&] {
+             if (act) {
+               double c, s;
+               if (rotation(a[mine.a * S + mine.a], a[mine.b * S + mine.b], a[mine.a * S + mine.b],
+                            mine.a > mine.b, &c, &s))
+                 rotated[sweep & 1] = 1;
+               cs[tid] = make_double2(c, s);
+               if constexpr (VEC == kVecRecord) {
+                 *rec = make_double2(c, s);
+                 rec += np;
+               }
+             }
+             mine.step(mm);
+           },
+           [] {});
+  } else if (wave < jw.rot + jw.blocks) {
+    const int nb = np * (np + 1) / 2, bt = tid - 64 * jw.rot, nbt = 64 * jw.blocks;
+    int bk[NB], bl[NB];
+#pragma unroll
+    for (int t = 0; t < NB; ++t) block_of(bt + t * nbt, np, &bk[t], &bl[t]);
+    Pair pk[NB], pl[NB];
+    double x[NB][4];
+    sweeps(
+        [&] {
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            pk[t] = Pair(mm, 0, bk[t]);
+            pl[t] = Pair(mm, 0, bl[t]);
+          }
+        },
+        [&] {
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            if (bt + t * nbt >= nb) continue;
+            const int ra = pk[t].a * S, rb = pk[t].b * S;
+            x[t][0] = a[ra + pl[t].a];
+            x[t][1] = a[ra + pl[t].b];
+            x[t][2] = a[rb + pl[t].a];
+            x[t][3] = a[rb + pl[t].b];
+          }
+        },
+        [&] {
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            if (bt + t * nbt < nb) {
+              const double2 ck = cs[bk[t]], cl = cs[bl[t]];
+              rot_block(ck.x, ck.y, cl.x, cl.y, x[t][0], x[t][1], x[t][2], x[t][3]);
+              const int ka = pk[t].a, kb = pk[t].b, la = pl[t].a, lb = pl[t].b;
+              const bool diag = bk[t] == bl[t];  // then entries 1 and 2 are a_pq, now 0
+              const double x1 = diag ? 0.0 : x[t][1], x2 = diag ? 0.0 : x[t][2];
+              a[ka * S + la] = x[t][0];
+              a[ka * S + lb] = x1;
+              a[kb * S + la] = x2;
+              a[kb * S + lb] = x[t][3];
+              a[la * S + ka] = x[t][0];
+              a[lb * S + ka] = x1;
+              a[la * S + kb] = x2;
+              a[lb * S + kb] = x[t][3];
+            }
+            pk[t].step(mm);
+            pl[t].step(mm);
+          }
+        });
+  } else if constexpr (VEC == kVecInline) {
+    // pair vl (fastest over the lanes), rows vi, vi + vrows, ...
+    const int vt = tid - 64 * (jw.rot + jw.blocks), vrows = (mm + kVRows - 1) / kVRows;
+    const int vl = vt % np, vi = vt / np;
+    const bool act = vi < vrows;
+    Pair vp;
+    double va[kVRows], vb[kVRows];
+    sweeps([&] { vp = Pair(mm, 0, vl); },
+           [&] {
+#pragma unroll
+             for (int r = 0; r < kVRows; ++r) {
+               const int i = min(vi + r * vrows, mm - 1) * mm;
+               va[r] = v[i + vp.a];
+               vb[r] = v[i + vp.b];
+             }
+           },
+           [&] {
+             const double2 c = cs[vl];
+#pragma unroll
+             for (int r = 0; r < kVRows; ++r) {
+               const int i = vi + r * vrows;
+               if (act && i < mm) {
+                 v[i * mm + vp.a] = c.x * va[r] - c.y * vb[r];
+                 v[i * mm + vp.b] = c.y * va[r] + c.x * vb[r];
+               }
+             }
+             vp.step(mm);
+           });
+  }
+  // the sweep that ended the loop is all identity and not recorded
+  if constexpr (VEC == kVecRecord)
+    if (tid == 0) o.info[0] = sweep * (mm - 1);
+  jacobi_sorted<VEC>(m, o, [&](int j) { return a[j * S + j]; }, v, mm);
+}
+
+// mm <= 192: the upper triangle packed (148 KB at 192), a_ij at off(i) + j, i <= j.
+// Bound by LDS access here, so blocks are read only when their rotations are known,
+// and a pair's indices and row offsets come from LDS with them.
+template <int VEC>
+__device__ __forceinline__ void jacobi_packed(int m, const double* __restrict__ A, int64_t lda,
+                                              const JacobiOut& o) {
+  extern __shared__ __align__(16) double sh[];
+  __shared__ int rotated[2];
+  constexpr int NB = 5;  // 96 * 97 / 2 blocks <= 5 * 1024
+  const int mm = m + (m & 1), np = mm / 2;
+  double2* cs = reinterpret_cast<double2*>(sh);   // rotation of each pair
+  int4* pr = reinterpret_cast<int4*>(cs + np);    // its p < q and their row offsets
+  double* a = reinterpret_cast<double*>(pr + np);
+  const int tid = threadIdx.x, nt = blockDim.x;
+  auto off = [&](int i) { return i * mm - ((i * (i + 1)) >> 1); };
+  for (int e = tid; e < mm * mm; e += nt) {
+    const int i = e / mm, j = e - i * mm;
+    if (i <= j) a[off(i) + j] = j < m ? A[(int64_t)i * lda + j] : 0.0;
+  }
+  const int nb = np * (np + 1) / 2;
+  int bk[NB], bl[NB];
+#pragma unroll
+  for (int t = 0; t < NB; ++t) block_of(tid + t * nt, np, &bk[t], &bl[t]);
+  if (tid < 2) rotated[tid] = 0;
+  __syncthreads();
+  int sweep = 0;
+  for (; sweep < kMaxSweeps; ++sweep) {
+    int* flag = &rotated[sweep & 1];
+    for (int round = 0; round < mm - 1; ++round) {
+      if (tid < np) {
+        const Pair t(mm, round, tid);
+        const int p = min(t.a, t.b), q = max(t.a, t.b), op = off(p), oq = off(q);
+        double c, s;
+        if (rotation(a[op + p], a[oq + q], a[op + q], false, &c, &s)) *flag = 1;
+        cs[tid] = make_double2(c, s);
+        pr[tid] = make_int4(p, q, op, oq);
+        if constexpr (VEC == kVecRecord)
+          o.rec[((int64_t)sweep * (mm - 1) + round) * np + tid] =
+              make_double2(c, t.a > t.b ? -s : s);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        if (tid + t * nt >= nb) continue;
+        const int4 P = pr[bk[t]], Q = pr[bl[t]];
+        const double2 ck = cs[bk[t]], cl = cs[bl[t]];
+        auto at = [&](int i, int oi, int j, int oj) { return i <= j ? oi + j : oj + i; };
+        const int ipp = at(P.x, P.z, Q.x, Q.z), ipq = at(P.x, P.z, Q.y, Q.w);
+        const int iqp = at(P.y, P.w, Q.x, Q.z), iqq = at(P.y, P.w, Q.y, Q.w);
+        double bpp = a[ipp], bpq = a[ipq], bqp = a[iqp], bqq = a[iqq];
+        rot_block(ck.x, ck.y, cl.x, cl.y, bpp, bpq, bqp, bqq);
+        const bool diag = bk[t] == bl[t];
+        a[ipp] = bpp;
+        a[iqq] = bqq;
+        a[ipq] = diag ? 0.0 : bpq;
+        a[iqp] = diag ? 0.0 : bqp;
+      }
+      __syncthreads();
+    }
+    const bool more = *flag != 0;
+    if (tid == 0) rotated[1 - (sweep & 1)] = 0;
+    __syncthreads();
+    if (!more) break;
+  }
+  if constexpr (VEC == kVecRecord)
+    if (tid == 0) o.info[0] = sweep * (mm - 1);
+  jacobi_sorted<VEC>(m, o, [&](int j) { return a[off(j) + j]; }, nullptr, mm);
+}
+
+// NB = 0: the packed form.
+template <int VEC, int NB>
+__device__ __forceinline__ void jacobi_body(int m, const double* __restrict__ A, int64_t lda,
+                                            const JacobiOut& o, const JacobiWaves& jw) {
+  if constexpr (NB == 0)
+    jacobi_packed<VEC>(m, A, lda, o);
+  else
+    jacobi_square<VEC, NB>(m, A, lda, o, jw);
+}
+
+template <int VEC, int NB>
+__global__ __launch_bounds__(1024) void k_jacobi_lds(int m, const double* __restrict__ A,
+                                                     int64_t lda, JacobiOut o, JacobiWaves jw) {
+  jacobi_body<VEC, NB>(m, A, lda, o, jw);
+}
+
+// Eigenvalues of many matrices, one workgroup each (EighItem).
+template <int NB>
+__global__ __launch_bounds__(1024) void k_jacobi_values(const double* __restrict__ A,
+                                                        const EighItem* __restrict__ items,
+                                                        double* __restrict__ w, JacobiWaves jw) {
+  const EighItem t = items[blockIdx.x];
+  JacobiOut o{};
+  o.w = w + t.w_at;
+  jacobi_body<kVecNone, NB>(t.dim, A + t.a_at, t.dim, o, jw);
+}
+
+// V from the recorded rotations: one wavefront applies all of them to its rows of
+// the identity, then stores the columns in the order of the eigenvalues.
+constexpr int kVecRows = 4;
+__global__ __launch_bounds__(64) void k_jacobi_vectors(int m, const double2* __restrict__ rec,
+                                                       const int* __restrict__ info,
+                                                       double* __restrict__ V, int64_t ldv) {
+  __shared__ double v[kVecRows][kLdsMax];
+  const int mm = m + (m & 1), np = mm / 2, lane = threadIdx.x;
+  const int row0 = blockIdx.x * kVecRows;
+  for (int e = lane; e < kVecRows * mm; e += 64) {
+    const int r = e / mm, j = e - r * mm;
+    v[r][j] = row0 + r == j ? 1.0 : 0.0;
+  }
+  const int rounds = info[0];
+  constexpr int kL = (kLdsMax / 2 + 63) / 64;  // pairs per lane
+  double2 next[kL];
+  auto fetch = [&](int rd) {
+#pragma unroll
+    for (int t = 0; t < kL; ++t) {
+      const int l = lane + 64 * t;
+      next[t] = l < np ? rec[(int64_t)rd * np + l] : make_double2(1.0, 0.0);
+    }
+  };
+  Pair pair[kL] = {Pair(mm, 0, min(lane, np - 1)), Pair(mm, 0, min(lane + 64, np - 1))};
+  static_assert(kL == 2, "pairs per lane");
+  if (rounds > 0) fetch(0);
+  __syncthreads();
+  for (int rd = 0; rd < rounds; ++rd) {
+    double2 c[kL];
+#pragma unroll
+    for (int t = 0; t < kL; ++t) c[t] = next[t];
+    if (rd + 1 < rounds) fetch(rd + 1);
+#pragma unroll
+    for (int t = 0; t < kL; ++t) {
+      if (lane + 64 * t < np && c[t].y != 0.0) {
+        const int p = pair[t].a, q = pair[t].b;
+#pragma unroll
+        for (int r = 0; r < kVecRows; ++r) {
+          const double vp = v[r][p], vq = v[r][q];
+          v[r][p] = c[t].x * vp - c[t].y * vq;
+          v[r][q] = c[t].y * vp + c[t].x * vq;
+        }
+      }
+      pair[t].step(mm);
+    }
+    __syncthreads();  // one wavefront: orders its LDS accesses
+  }
+  for (int e = lane; e < kVecRows * m; e += 64) {
+    const int r = e / m, j = e - r * m;
+    if (row0 + r < m) V[(int64_t)(row0 + r) * ldv + info[1 + j]] = v[r][j];
   }
 }
 
@@ -175,8 +476,8 @@ __global__ __launch_bounds__(256) void k_jacobi_round(int mm, int round,
     pair_of(mm, round, k, &pk, &qk);
     pair_of(mm, round, l, &pl, &ql);
     double ck, sk, cl, sl;
-    const bool rk = rotation(ain[pk * mm + pk], ain[qk * mm + qk], ain[pk * mm + qk], &ck, &sk);
-    rotation(ain[pl * mm + pl], ain[ql * mm + ql], ain[pl * mm + ql], &cl, &sl);
+    const bool rk = rotation(ain[pk * mm + pk], ain[qk * mm + qk], ain[pk * mm + qk], false, &ck, &sk);
+    rotation(ain[pl * mm + pl], ain[ql * mm + ql], ain[pl * mm + ql], false, &cl, &sl);
     if (k == l && rk) atomicAdd(nrot, 1);
     double bpp = ain[pk * mm + pl], bpq = ain[pk * mm + ql], bqp = ain[qk * mm + pl],
            bqq = ain[qk * mm + ql];
@@ -195,7 +496,7 @@ __global__ __launch_bounds__(256) void k_jacobi_round(int mm, int round,
     int pl, ql;
     pair_of(mm, round, l, &pl, &ql);
     double cl, sl;
-    rotation(ain[pl * mm + pl], ain[ql * mm + ql], ain[pl * mm + ql], &cl, &sl);
+    rotation(ain[pl * mm + pl], ain[ql * mm + ql], ain[pl * mm + ql], false, &cl, &sl);
     const double vp = v[i * mm + pl], vq = v[i * mm + ql];
     v[i * mm + pl] = cl * vp - sl * vq;
     v[i * mm + ql] = sl * vp + cl * vq;
@@ -339,7 +640,49 @@ inline unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 size_t small_eigh_work_bytes(int m) {
   const int64_t mm = m + (m & 1);
-  return (size_t)(3 * mm * mm) * sizeof(double) + 256;
+  size_t bytes = (size_t)(3 * mm * mm) * sizeof(double) + 256;
+  if (mm <= kLdsMax)  // every round's rotations, their number and the column order
+    bytes = std::max(bytes, (size_t)kMaxSweeps * (mm - 1) * (mm / 2) * sizeof(double2) +
+                                (size_t)(mm + 1) * sizeof(int) + 256);
+  return bytes;
+}
+
+namespace {
+
+template <class K, class... Args>
+void launch_jacobi_lds(K kernel, int count, int mm, bool vec, hipStream_t s, Args... args) {
+  const size_t shm = jacobi_lds_bytes(mm, vec);
+  MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
+  const JacobiWaves jw = jacobi_waves(mm, vec);
+  hipLaunchKernelGGL(kernel, dim3(count), dim3(jw.threads()), shm, s, args..., jw);
+  MBL_CHECK_LAUNCH();
+}
+
+// Blocks per thread of the square form, 0: the packed form.
+template <class F>
+void by_blocks(int mm, F&& f) {
+  const int bt = 64 * jacobi_waves(mm, false).blocks, per = (jacobi_blocks(mm) + bt - 1) / bt;
+  if (mm > kSquareMax)
+    f(std::integral_constant<int, 0>{});
+  else if (per <= 1)
+    f(std::integral_constant<int, 1>{});
+  else if (per <= 2)
+    f(std::integral_constant<int, 2>{});
+  else
+    f(std::integral_constant<int, 3>{});
+}
+
+}  // namespace
+
+void eigh_values(int count, int max_dim, const double* A, const EighItem* items_dev, double* w,
+                 hipStream_t s) {
+  if (count == 0) return;
+  const int mm = max_dim + (max_dim & 1);
+  if (mm > kLdsMax) fail(MBL_EINTERNAL, "eigh_values: matrix too large");
+  by_blocks(mm, [&](auto nb) {
+    launch_jacobi_lds(&k_jacobi_values<decltype(nb)::value>, count, mm, false, s, A, items_dev, w);
+  });
 }
 
 void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64_t ldv,
@@ -347,7 +690,7 @@ void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64
   PhaseTick tick(PhaseClock::SMALL, s);
   if (m <= 0) return;
   const int mm = m + (m & 1);
-  const int max_sweeps = 30;
+  const int max_sweeps = kMaxSweeps;
   if (m == 1) {
     MBL_HIP(hipMemcpyAsync(w, A, sizeof(double), hipMemcpyDeviceToDevice, s));
     if (V) {
@@ -357,26 +700,34 @@ void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64
     }
     return;
   }
-  if (!V && mm <= 2 * kLdsPairs) {
-    // eigenvalues only: A alone in LDS
-    const size_t shm = (size_t)mm * mm * sizeof(double);
-    MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_jacobi_lds<false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
-    hipLaunchKernelGGL(k_jacobi_lds<false>, dim3(1), dim3(1024), shm, s, m, A, lda, w,
-                       (double*)nullptr, (int64_t)0, max_sweeps);
-    MBL_CHECK_LAUNCH();
+  if (mm <= kLdsMax) {
+    JacobiOut o{};
+    o.w = w;
+    o.V = V;
+    o.ldv = ldv;
+    if (V && mm <= kInlineMax) {
+      launch_jacobi_lds(&k_jacobi_lds<kVecInline, 1>, 1, mm, true, s, m, A, lda, o);
+      return;
+    }
+    if (V) {
+      o.rec = reinterpret_cast<double2*>(work);
+      o.info = reinterpret_cast<int*>(o.rec + (size_t)kMaxSweeps * (mm - 1) * (mm / 2));
+    }
+    by_blocks(mm, [&](auto nb) {
+      constexpr int NB = decltype(nb)::value;
+      if (V)
+        launch_jacobi_lds(&k_jacobi_lds<kVecRecord, NB>, 1, mm, false, s, m, A, lda, o);
+      else
+        launch_jacobi_lds(&k_jacobi_lds<kVecNone, NB>, 1, mm, false, s, m, A, lda, o);
+    });
+    if (V) {
+      hipLaunchKernelGGL(k_jacobi_vectors, dim3((m + kVecRows - 1) / kVecRows), dim3(64), 0, s, m,
+                         o.rec, o.info, V, ldv);
+      MBL_CHECK_LAUNCH();
+    }
     return;
   }
-  if (!V) fail(MBL_EINTERNAL, "small_eigh: eigenvectors are needed above 128");
-  if (mm <= 96) {
-    const size_t shm = (size_t)2 * mm * mm * sizeof(double);
-    MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_jacobi_lds<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
-    hipLaunchKernelGGL(k_jacobi_lds<true>, dim3(1), dim3(1024), shm, s, m, A, lda, w, V, ldv,
-                       max_sweeps);
-    MBL_CHECK_LAUNCH();
-    return;
-  }
+  if (!V) fail(MBL_EINTERNAL, "small_eigh: eigenvectors are needed above 192");
   double* a0 = work;
   double* a1 = work + (size_t)mm * mm;
   double* v = work + (size_t)2 * mm * mm;
