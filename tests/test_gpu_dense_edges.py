@@ -1,12 +1,16 @@
-"""The small eigensolver at the sizes where its kernels change form, against numpy.
+"""The small eigensolver and the entropy at the sizes where their kernels change
+form, against numpy and the oracle.
 
 Eigenvalues to 1e-12 of the largest, vectors orthonormal to 1e-12 and with residual
-1e-11 of the largest eigenvalue (the bars of test_gpu_kernels.py).
+1e-11 of the largest eigenvalue (the bars of test_gpu_kernels.py); entropies to 1e-10.
 """
 
 import numpy as np
 import pytest
 import torch
+
+from oracle import basis, observables
+from paper_2012_00217_amd import workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +59,21 @@ def test_small_eigh_extreme_scales(scale):
         np.testing.assert_allclose(w.cpu().numpy() / scale, np.linalg.eigvalsh(A), rtol=0,
                                    atol=1e-11 * m)
         np.testing.assert_allclose((V.T @ V).cpu().numpy(), np.eye(m), atol=1e-12)
+
+
+@pytest.mark.parametrize("L,Sz,cut,nev", [(10, 0.0, 1, 3), (10, 0.0, 9, 1), (11, 1.5, 4, 17),
+                                          (14, -3.0, 6, 2), (22, 0.0, 3, 50), (20, 0.0, 10, 2)])
+def test_entropy_blocks(L, Sz, cut, nev):
+    """Cuts at the ends, S^z != 0, more vectors than one chunk takes (L = 22), blocks
+    above and below the size that is solved in one launch (L = 20)."""
+    H = api.Hamiltonian(L, workloads.disorder(L, 2.0, 0), Sz=Sz)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    V = torch.randn(H.n, nev + 3, dtype=torch.float64, device=DEV, generator=g)[:, 2:2 + nev]
+    V = V / V.norm(dim=0)
+    S = H.entanglement_entropy(V, cut)
+    st = basis.enumerate_sector(L, basis.nup_from_sz(L, Sz))
+    for j in sorted({0, 1, 42, 43, nev - 1}):
+        if j < nev:
+            want = observables.entanglement_entropy(V[:, j].cpu().numpy(), st, L, cut)
+            assert abs(S[j] - want) <= 1e-10
