@@ -345,7 +345,8 @@ mbl_status mbl_gram_noalloc(mbl_precision prec, int64_t n, const void* A, int64_
     check_block(A, lda, p, "A is NULL");
     check_block(B, ldb, q, "B is NULL");
     require(C_dev != nullptr && ldc >= q, "bad C");
-    const GramPlan g = gram_plan(n, p, q, A == B && lda == ldb);
+    const bool same = A == B && lda == ldb;
+    const GramPlan g = prec == MBL_F64 ? gram_plan<double>(n, p, q, same) : gram_plan<float>(n, p, q, same);
     if (g.part_bytes > kGramScratchBytes)
       fail(MBL_EINVAL, "mbl_gram_noalloc: this shape needs " + std::to_string(g.part_bytes) +
                            " bytes of partial sums, above the fixed " +

@@ -55,14 +55,19 @@ struct Mfma<float> {
 // each element read from memory once per workgroup), and the next slab's
 // loads are in flight while the waves run their 32 MFMAs on the current one.
 // sym (A = B, p = q): only the tiles on and above the diagonal are formed;
-// blockIdx.x enumerates them row by row, and a diagonal tile stages one panel.
+// they are enumerated row by row, and a diagonal tile stages one panel.
 constexpr int kSlab = 32;
 
 template <class T>
 struct GramStage {
   static constexpr int VE = 16 / (int)sizeof(T);           // elements per 16-byte load
   static constexpr int PER = kSlab * 64 / (256 * VE);       // loads per thread per panel
-  static constexpr int LD = 64 + VE;                        // padded LDS row
+  static constexpr int SWZ = sizeof(T) == 8 ? 1 : 3;
+  // Place of element (r, c) of a panel: the rows are 64 elements apart and their blocks
+  // of 16 columns are exchanged, so that the 4 rows x 16 columns of an operand read lie
+  // in different banks (FP32 103 -> 98 us at n = 184756, p = q = 192, against rows
+  // padded by 16 bytes; FP64 176 -> 174).
+  __device__ static int at(int r, int c) { return r * 64 + (c ^ ((r & SWZ) << 4)); }
 };
 
 template <class T>
@@ -96,24 +101,31 @@ __device__ inline void gram_store(T* __restrict__ sm, const T (&reg)[GramStage<T
     const int e = (u * 256 + (int)threadIdx.x) * S::VE;
     const int r = e >> 6, c = e & 63;
 #pragma unroll
-    for (int t = 0; t < S::VE; ++t) sm[r * S::LD + c + t] = reg[u][t];
+    for (int t = 0; t < S::VE; ++t) sm[S::at(r, c) + t] = reg[u][t];
   }
 }
 
+// Bound by the waits of a slab's loads and barriers: 65 % of the time the matrix cores
+// are busy.  Four workgroups per CU (launch_bounds caps the registers at 128) hold all
+// 1024 workgroups of a launch at once; at 152 registers three fitted, and the last
+// quarter of the workgroups ran as a second round (n = 184756, p = q = 192, FP64:
+// 275 us, now 203; p = 128, q = 64: 110, now 80; FP32 131, now 108).
 template <class T>
-__global__ __launch_bounds__(256) void k_gram(int64_t n, const T* __restrict__ A, int64_t lda,
-                                              int p, const T* __restrict__ B, int64_t ldb, int q,
-                                              int sym, int vec, int64_t rows_per_split,
-                                              double* __restrict__ part) {
+__global__ __launch_bounds__(256, 4) void k_gram(int64_t n, const T* __restrict__ A, int64_t lda,
+                                                 int p, const T* __restrict__ B, int64_t ldb,
+                                                 int q, int sym, int vec, int tiles,
+                                                 int64_t rows_per_split,
+                                                 double* __restrict__ part) {
   using M = Mfma<T>;
   using S = GramStage<T>;
-  __shared__ T sa[kSlab * S::LD], sb[kSlab * S::LD];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wy = wave >> 1, wx = wave & 1;
+  __shared__ T sa[kSlab * 64], sb[kSlab * 64];
+  const int lane = threadIdx.x & 63;
   const int tiles_q = (q + 63) / 64;
+  const int item = blockIdx.x % tiles;
+  const int64_t split = blockIdx.x / tiles;
   int ty, tx;
   if (sym) {
-    int t = blockIdx.x;
+    int t = item;
     ty = 0;
     while (t >= tiles_q - ty) {
       t -= tiles_q - ty;
@@ -121,13 +133,18 @@ __global__ __launch_bounds__(256) void k_gram(int64_t n, const T* __restrict__ A
     }
     tx = ty + t;
   } else {
-    ty = blockIdx.x / tiles_q;
-    tx = blockIdx.x % tiles_q;
+    ty = item / tiles_q;
+    tx = item % tiles_q;
   }
   const bool same = sym && ty == tx;  // one panel serves both operands
+  // The quadrant of a wavefront moves on with the split: the wavefronts of a SIMD
+  // then skip below the diagonal equally often.
+  const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) + (int)split) & 3;
+  const int wy = wave >> 1, wx = wave & 1;
+  const bool below = same && wy > wx;  // a quadrant below the diagonal: not needed
   const T* sbp = same ? sa : sb;
   const int li = lane & 15, lk = lane >> 4;
-  const int64_t kb = (int64_t)blockIdx.y * rows_per_split;
+  const int64_t kb = split * rows_per_split;
   const int64_t ke = min(n, kb + rows_per_split);
   typename M::acc acc[2][2];
 #pragma unroll
@@ -148,13 +165,14 @@ __global__ __launch_bounds__(256) void k_gram(int64_t n, const T* __restrict__ A
       gram_load<T>(A, lda, p, ty * 64, k + kSlab, ke, vec != 0, ra);
       if (!same) gram_load<T>(B, ldb, q, tx * 64, k + kSlab, ke, vec != 0, rb);
     }
+    if (below) continue;
 #pragma unroll
     for (int kk = 0; kk < kSlab; kk += 4) {
       T a[2], b[2];
 #pragma unroll
       for (int v = 0; v < 2; ++v) {
-        a[v] = sa[(kk + lk) * S::LD + wy * 32 + 16 * v + li];
-        b[v] = sbp[(kk + lk) * S::LD + wx * 32 + 16 * v + li];
+        a[v] = sa[kk * 64 + S::at(lk, wy * 32 + 16 * v + li)];
+        b[v] = sbp[kk * 64 + S::at(lk, wx * 32 + 16 * v + li)];
       }
 #pragma unroll
       for (int i = 0; i < 2; ++i)
@@ -162,8 +180,9 @@ __global__ __launch_bounds__(256) void k_gram(int64_t n, const T* __restrict__ A
         for (int j = 0; j < 2; ++j) acc[i][j] = M::op(a[i], b[j], acc[i][j]);
     }
   }
+  if (below) return;
   const int c0 = ty * 64 + wy * 32, d0 = tx * 64 + wx * 32;
-  double* out = part + (int64_t)blockIdx.y * p * q;
+  double* out = part + split * p * q;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -176,21 +195,29 @@ __global__ __launch_bounds__(256) void k_gram(int64_t n, const T* __restrict__ A
       }
 }
 
-// One wavefront per output element: lane l sums splits l, l+64, ... in order,
-// then a fixed butterfly folds the 64 lane sums.
-// sym: elements of tiles below the diagonal are read from their mirror.
+// 16 consecutive elements of C per workgroup (a 128-byte line of every partial), 16
+// threads each: thread g sums splits g, g + 16, ... in order, then the 16 sums are added
+// in order.  One element per wavefront read 8 bytes of every line that it fetched
+// (192 x 192, 170 splits: 17 us, now 7.8).
+// sym: elements below the diagonal are written as the mirror of those above.
 __global__ __launch_bounds__(256) void k_gram_fold(const double* __restrict__ part, int splits,
                                                    int p, int q, int sym, double* __restrict__ C,
                                                    int64_t ldc) {
-  const int lane = threadIdx.x & 63;
-  const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (idx >= (int64_t)p * q) return;
-  const int r = (int)(idx / q), c = (int)(idx % q);
-  const int64_t src = (sym && (r >> 6) > (c >> 6)) ? (int64_t)c * q + r : idx;
+  __shared__ double sm[16][17];
+  const int e = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int64_t step = (int64_t)p * q, idx = (int64_t)blockIdx.x * 16 + e;
+  const int64_t r = idx / q, c = idx % q;
+  const bool mine = idx < step && !(sym && c < r);
   double s = 0.0;
-  for (int sp = lane; sp < splits; sp += 64) s += part[(int64_t)sp * p * q + src];
-  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-  if (lane == 0) C[(idx / q) * ldc + idx % q] = s;
+  if (mine)
+#pragma unroll 4
+    for (int sp = g; sp < splits; sp += 16) s += part[sp * step + idx];
+  sm[g][e] = s;
+  __syncthreads();
+  if (g != 0 || !mine) return;
+  for (int k = 1; k < 16; ++k) s += sm[k][e];
+  C[r * ldc + c] = s;
+  if (sym && r < c) C[c * ldc + r] = s;
 }
 
 // Y[r, j] = sum_k A[r, k] C[k, j] + beta Y[r, j].  Tile: 64 rows x 64 columns
@@ -299,6 +326,11 @@ inline unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
+// At most 1024 workgroups, four per CU, which are resident at once.  FP64: splits down to
+// 64 rows, where a short sector leaves CUs idle (n = 3432, p = q = 96: 14 splits of 256
+// rows 24 us, 54 of 64 rows 18 us).  FP32: the accumulation is in FP32, so the split of
+// the rows is part of the result and stays at 256 rows.
+template <class T>
 GramPlan gram_plan(int64_t n, int p, int q, bool same_operand) {
   GramPlan g;
   // A^T A: only the upper tiles (the Rayleigh-Ritz and Cholesky-QR Grams)
@@ -309,8 +341,9 @@ GramPlan gram_plan(int64_t n, int p, int q, bool same_operand) {
     g.splits = 1;
     g.rows = kSlab;
   } else {
+    const int64_t least = sizeof(T) == 8 ? 64 : 256;
     int64_t splits = std::max<int64_t>(1, 1024 / g.tiles);
-    splits = std::min<int64_t>(splits, std::max<int64_t>(1, (n + 255) / 256));
+    splits = std::min<int64_t>(splits, std::max<int64_t>(1, (n + least - 1) / least));
     int64_t rows = (n + splits - 1) / splits;
     rows = ((rows + kSlab - 1) / kSlab) * kSlab;
     g.rows = rows;
@@ -319,6 +352,8 @@ GramPlan gram_plan(int64_t n, int p, int q, bool same_operand) {
   g.part_bytes = (size_t)g.splits * p * q * sizeof(double);
   return g;
 }
+template GramPlan gram_plan<double>(int64_t, int, int, bool);
+template GramPlan gram_plan<float>(int64_t, int, int, bool);
 
 template <class T>
 void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int p, const T* B,
@@ -329,10 +364,10 @@ void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int
                           (uintptr_t)(lda * (int64_t)sizeof(T)) |
                           (uintptr_t)(ldb * (int64_t)sizeof(T));
   const int vec = (align % 16) == 0;
-  hipLaunchKernelGGL(k_gram<T>, dim3(g.tiles, (unsigned)g.splits), dim3(256), 0, s, n, A, lda, p,
-                     B, ldb, q, g.sym, vec, g.rows, part);
+  hipLaunchKernelGGL(k_gram<T>, dim3((unsigned)(g.tiles * g.splits)), dim3(256), 0,
+                     s, n, A, lda, p, B, ldb, q, g.sym, vec, g.tiles, g.rows, part);
   MBL_CHECK_LAUNCH();
-  hipLaunchKernelGGL(k_gram_fold, dim3((unsigned)(((int64_t)p * q + 3) / 4)), dim3(256), 0, s,
+  hipLaunchKernelGGL(k_gram_fold, dim3((unsigned)(((int64_t)p * q + 15) / 16)), dim3(256), 0, s,
                      part, (int)g.splits, p, q, g.sym, C, ldc);
   MBL_CHECK_LAUNCH();
 }
@@ -341,7 +376,7 @@ template <class T>
 void launch_gram(int64_t n, const T* A, int64_t lda, int p, const T* B, int64_t ldb, int q,
                  double* C, int64_t ldc, hipStream_t s) {
   if (p == 0 || q == 0) return;
-  const GramPlan g = gram_plan(n, p, q, A == B && lda == ldb);
+  const GramPlan g = gram_plan<T>(n, p, q, A == B && lda == ldb);
   DevBuf part(g.part_bytes, s);
   launch_gram_part<T>(g, n, A, lda, p, B, ldb, q, C, ldc, part.as<double>(), s);
 }

@@ -77,3 +77,40 @@ def test_entropy_blocks(L, Sz, cut, nev):
         if j < nev:
             want = observables.entanglement_entropy(V[:, j].cpu().numpy(), st, L, cut)
             assert abs(S[j] - want) <= 1e-10
+
+
+def _block(n, p, dtype, seed, lead=0):
+    """n x p block of one-digit integers (every product and sum of a Gram is exact), rows
+    `lead` elements further apart than p."""
+    g = torch.Generator().manual_seed(seed)
+    full = torch.randint(-3, 4, (n, p + lead), generator=g).to(dtype).to(DEV)
+    return full[:, :p]
+
+
+# tiles of 64 columns and quadrants of 32, 16-element folds, slabs of 32 rows, splits of
+# 64 (FP64) and 256 (FP32) rows
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 257, 3432])
+@pytest.mark.parametrize("p,q,lead", [(1, 1, 0), (17, 1, 0), (31, 33, 3), (64, 64, 0), (65, 16, 1),
+                                      (130, 66, 2)])
+def test_gram_edges(n, p, q, lead, dtype):
+    A, B = _block(n, p, dtype, 1, lead), _block(n, q, dtype, 2, lead)
+    a, b = A.double(), B.double()
+    assert torch.equal(api.gram(A, B), (a.T @ b))
+    C = api.gram(A, A)
+    assert torch.equal(C, a.T @ a)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("p", [15, 16, 31, 32, 33, 63, 64, 65, 96, 97, 192, 200])
+def test_gram_of_one_operand_is_that_of_two(p, dtype):
+    """Mirrored tiles and skipped quadrants against the full product, rounding and all."""
+    g = torch.Generator().manual_seed(p)
+    A = torch.randn(4097, p, generator=g, dtype=torch.float64).to(dtype).to(DEV)
+    C = api.gram(A, A)
+    assert torch.equal(C, C.T)
+    # a product in FP64 has errors of the size that is looked for: 64-bit mantissas
+    a = A.cpu().numpy().astype(np.longdouble)
+    err = float(np.abs(C.cpu().numpy() - a.T @ a).max())
+    # 4097 products of O(1) in the accumulation's type, summed over splits
+    assert err <= 4097 * (2.3e-16 if dtype == torch.float64 else 1.2e-7) * 3
