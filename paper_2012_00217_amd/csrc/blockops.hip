@@ -220,58 +220,121 @@ __global__ __launch_bounds__(256) void k_gram_fold(const double* __restrict__ pa
   if (sym && r < c) C[c * ldc + r] = s;
 }
 
-// Y[r, j] = sum_k A[r, k] C[k, j] + beta Y[r, j].  Tile: 64 rows x 64 columns
-// per workgroup, 32-deep K slices in LDS; each thread owns 4 x 4 outputs.
+// Y[r, j] = sum_k A[r, k] C[k, j] + beta Y[r, j] on the matrix cores.
+//
+// A wavefront owns 16 rows x 16 NB columns.  The rows of A go from memory straight
+// into the operand registers: the sum over k may run in any order, so lane (i, g) of the
+// 16 x 4 operand takes the 16-byte piece g of a slab of its row (k = 2g, 2g + 1 in FP64,
+// 4g .. 4g + 3 in FP32) and step t of the slab multiplies element t of every piece.  Four
+// slabs are one group; the next group's loads (of the next tile at a row's end) are in
+// flight while the group is multiplied.  C stands in LDS, rounded to T, in chunks of kc
+// rows of k; when all of C fits it is loaded once and the wavefronts run over their
+// tiles without a barrier.
+//
+// Bound by memory (378 MB) and the matrix cores (4.5 GFLOP FP64) about equally at
+// n = 184756, 192 -> 64 columns: 137 us a call; the vector-unit form that staged A through
+// LDS took 237.  64 -> 64: 88, now 48; FP32 192 -> 64: 131, now 78.
 template <class T>
-__global__ __launch_bounds__(256) void k_combine(int64_t n, const T* __restrict__ A, int64_t lda,
+struct CombineStage {
+  static constexpr int VE = 16 / (int)sizeof(T);  // elements per 16-byte piece
+  static constexpr int SL = 4 * VE;               // k per slab
+  static constexpr int GK = 4 * SL;               // k per group
+  // Place of C[k][c] in a chunk of rows of W elements: the 4 rows of an operand, VE apart,
+  // go to different banks.
+  template <int W>
+  __device__ static int at(int k, int c) {
+    constexpr int M = (sizeof(T) == 8 ? 2 : 4) < W / 16 ? (sizeof(T) == 8 ? 2 : 4) : W / 16;
+    return k * W + (c ^ (((k / VE) & (M - 1)) << 4));
+  }
+};
+
+template <class T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* __restrict__ A, int64_t lda,
                                                  int p, const double* __restrict__ Cm,
                                                  int64_t ldc, T* __restrict__ Y, int64_t ldy,
-                                                 int q, double beta) {
-  __shared__ T As[32][64 + 1];  // [k][row]
-  __shared__ T Cs[32][64];      // [k][col]
-  const int tid = threadIdx.x;
-  const int64_t r0 = (int64_t)blockIdx.x * 64;
-  const int c0 = blockIdx.y * 64;
-  const int tr = (tid >> 4) * 4, tc = (tid & 15) * 4;
-  T acc[4][4];
+                                                 int q, double beta, int vec, int kc,
+                                                 int64_t tiles) {
+  using M = Mfma<T>;
+  using S = CombineStage<T>;
+  constexpr int VE = S::VE, SL = S::SL, GK = S::GK, W = 16 * NB;
+  extern __shared__ __align__(16) unsigned char combine_lds[];
+  T* Cs = reinterpret_cast<T*>(combine_lds);  // [kc][W]
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = blockIdx.y * W;
+  const int64_t stride = (int64_t)gridDim.x * NW;
+  typedef T vec_t __attribute__((ext_vector_type(VE)));
+
+  auto fetch = [&](vec_t (&reg)[4], int64_t tile, int k0) {
+    const T* src = A + min(tile * 16 + li, n - 1) * lda;  // rows beyond n are not stored
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int u = 0; u < 4; ++u) {
+      const int k = k0 + u * SL + lk * VE;
+      if (vec) {  // p is a multiple of VE
+        const vec_t v = *reinterpret_cast<const vec_t*>(src + (k < p ? k : 0));
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = (T)0;
-  for (int k0 = 0; k0 < p; k0 += 32) {
-    for (int e = tid; e < 32 * 64; e += 256) {
-      const int rr = e >> 5, kk = e & 31;  // coalesced along k within a row
-      const int64_t row = r0 + rr;
-      const int col = k0 + kk;
-      As[kk][rr] = (row < n && col < p) ? A[row * lda + col] : (T)0;
-      const int ck = e >> 6, cc = e & 63;
-      Cs[ck][cc] = (k0 + ck < p && c0 + cc < q) ? (T)Cm[(int64_t)(k0 + ck) * ldc + c0 + cc] : (T)0;
+        for (int t = 0; t < VE; ++t) reg[u][t] = k < p ? v[t] : (T)0;
+      } else {
+#pragma unroll
+        for (int t = 0; t < VE; ++t) {
+          const T v = src[k + t < p ? k + t : 0];
+          reg[u][t] = k + t < p ? v : (T)0;
+        }
+      }
     }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      T av[4], cv[4];
+  };
+
+  vec_t nxt[4];
+  int64_t tile = (int64_t)blockIdx.x * NW + wave;
+  if (p > 0) fetch(nxt, tile, 0);
+  // every wavefront of the workgroup makes the same number of rounds (barriers)
+  for (int64_t base = (int64_t)blockIdx.x * NW; base < tiles; base += stride, tile += stride) {
+    typename M::acc acc[NB];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = As[kk][tr + i];
+    for (int j = 0; j < NB; ++j) acc[j] = typename M::acc{0, 0, 0, 0};
+    for (int k0 = 0; k0 < p; k0 += GK) {
+      const int kl = k0 % kc;
+      if (kl == 0 && (kc < p || base == (int64_t)blockIdx.x * NW)) {
+        __syncthreads();  // the wavefronts are done with the chunk before
+        for (int e = threadIdx.x; e < kc * W; e += 64 * NW) {
+          const int k = e / W, c = e % W;
+          Cs[S::template at<W>(k, c)] =
+              (k0 + k < p && c0 + c < q) ? (T)Cm[(int64_t)(k0 + k) * ldc + c0 + c] : (T)0;
+        }
+        __syncthreads();
+      }
+      vec_t cur[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cv[j] = Cs[kk][tc + j];
+      for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
+      if (k0 + GK < p)
+        fetch(nxt, tile, k0 + GK);
+      else
+        fetch(nxt, tile + stride, 0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int u = 0; u < 4; ++u) {
+        if (k0 + u * SL >= p) break;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * cv[j];
+        for (int t = 0; t < VE; ++t) {
+          T b[NB];
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+            b[j] = Cs[S::template at<W>(kl + u * SL + lk * VE + t, 16 * j + li)];
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[j] = M::op(cur[u][t], b[j], acc[j]);
+        }
+      }
     }
-    __syncthreads();
-  }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t row = r0 + tr + i;
-    if (row >= n) continue;
+    for (int v = 0; v < 4; ++v) {
+      const int64_t row = tile * 16 + M::row(lk, v);
+      if (row >= n) continue;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = c0 + tc + j;
-      if (col >= q) continue;
-      T* y = Y + row * ldy + col;
-      *y = (beta == 0.0) ? acc[i][j] : (T)(acc[i][j] + (T)beta * *y);
+      for (int j = 0; j < NB; ++j) {
+        const int c = c0 + 16 * j + li;
+        if (c >= q) continue;
+        T* y = Y + row * ldy + c;
+        *y = (beta == 0.0) ? acc[j][v] : (T)(acc[j][v] + (T)beta * *y);
+      }
     }
   }
 }
@@ -410,13 +473,45 @@ double* gram_scratch() {
   return g_scratch[dev];
 }
 
+template <class T, int NB, int NW>
+void launch_combine_as(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc,
+                       T* Y, int64_t ldy, int q, double beta, hipStream_t s) {
+  using S = CombineStage<T>;
+  constexpr size_t kLds = 96 * 1024;  // p = 192 of 64 FP64 columns in one chunk
+  constexpr int W = 16 * NB;
+  const int kc = (int)std::min<int64_t>(kLds / (W * sizeof(T)),
+                                        std::max<int64_t>(1, (p + S::GK - 1) / S::GK) * S::GK);
+  const size_t lds = (size_t)kc * W * sizeof(T);
+  const int64_t tiles = (n + 15) / 16;
+  const int64_t cols = (q + W - 1) / W;
+  // as many workgroups as are resident at once: each loads C once
+  const int64_t per_cu = std::min<int64_t>(16 / NW, (160 * 1024) / (int64_t)lds);
+  const int64_t grid = std::min<int64_t>((tiles + NW - 1) / NW,
+                                         std::max<int64_t>(1, 256 * per_cu / cols));
+  const uintptr_t align = reinterpret_cast<uintptr_t>(A) | (uintptr_t)(lda * (int64_t)sizeof(T)) |
+                          (uintptr_t)((int64_t)p * (int64_t)sizeof(T));
+  if (lds > 64 * 1024)
+    MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_combine<T, NB, NW>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL((k_combine<T, NB, NW>), dim3((unsigned)grid, (unsigned)cols), dim3(64 * NW),
+                     lds, s, n, A, lda, p, C, ldc, Y, ldy, q, beta, (align % 16) == 0 ? 1 : 0, kc,
+                     tiles);
+  MBL_CHECK_LAUNCH();
+}
+
 template <class T>
 void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc, T* Y,
                     int64_t ldy, int q, double beta, hipStream_t s) {
   if (n == 0 || q == 0) return;
-  hipLaunchKernelGGL(k_combine<T>, dim3((unsigned)((n + 63) / 64), (unsigned)((q + 63) / 64)),
-                     dim3(256), 0, s, n, A, lda, p, C, ldc, Y, ldy, q, beta);
-  MBL_CHECK_LAUNCH();
+  // Wide: all 64 columns in one wavefront read A once, and 16 wavefronts share a C of up to
+  // 96 KB (192 -> 64 columns, n = 184756, FP64: 137 us, two blocks of 32 columns 150).
+  // Narrow: no work on absent columns (51 -> 17, n = 705432: 115 us, wide 143), and for
+  // short sectors less C per workgroup and more workgroups (96 -> 32, n = 3432: 13 us,
+  // wide 23).
+  if (q > 32 && n >= 32768)
+    launch_combine_as<T, 4, 16>(n, A, lda, p, C, ldc, Y, ldy, q, beta, s);
+  else
+    launch_combine_as<T, 2, 8>(n, A, lda, p, C, ldc, Y, ldy, q, beta, s);
 }
 
 template <class S, class D>

@@ -114,3 +114,29 @@ def test_gram_of_one_operand_is_that_of_two(p, dtype):
     err = float(np.abs(C.cpu().numpy() - a.T @ a).max())
     # 4097 products of O(1) in the accumulation's type, summed over splits
     assert err <= 4097 * (2.3e-16 if dtype == torch.float64 else 1.2e-7) * 3
+
+
+# tiles of 16 rows, 32 or 64 columns a wavefront, slabs of 8 (FP64) or 16 columns of A,
+# groups of 32 or 64, chunks of C of 192 to 768; 32768 rows to the wide form
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n", [1, 15, 17, 130, 32767, 32768, 32785])
+@pytest.mark.parametrize("p,q,lead", [(1, 1, 0), (3, 17, 1), (8, 32, 0), (33, 33, 3), (64, 64, 0),
+                                      (97, 65, 2), (192, 64, 0), (193, 130, 1), (402, 34, 0),
+                                      (840, 3, 4)])
+def test_block_combine_edges(n, p, q, lead, dtype):
+    A = _block(n, p, dtype, 3, lead)
+    Cm = _block(p, q, torch.float64, 4)
+    Y = api.block_combine(A, Cm)
+    assert Y.dtype == dtype
+    assert torch.equal(Y.double(), A.double() @ Cm)
+
+
+def test_block_combine_keeps_non_finite_rows_apart():
+    """Padding rows, columns and slabs take nothing from their neighbours."""
+    A = torch.ones(40, 5, dtype=torch.float64, device=DEV)
+    A[39, 0] = float("nan")
+    A[7, 4] = float("inf")
+    Y = api.block_combine(A, torch.ones(5, 3, dtype=torch.float64, device=DEV)).cpu()
+    good = [r for r in range(40) if r not in (7, 39)]
+    assert torch.equal(Y[good], torch.full((38, 3), 5.0, dtype=torch.float64))
+    assert torch.isnan(Y[39]).all() and torch.isinf(Y[7]).all()
