@@ -118,10 +118,14 @@ __device__ inline double wave_cols(const double (&v)[VE]) {
 // together in the row order, which keeps their common neighbours in the L2.  Each
 // tile has its own partial sums, so the result does not depend on who took it.
 //
-// Bound: L2 misses.  Measured with 64 FP32 columns at L = 24 (n = 2,704,156,
-// 692 MB per vector): taken in order the tiles fetch 2.07 GB per apply1, 3.0 times
-// the gathered vector; dealt out in a fixed stride, where workgroups with small
-// tiles run ahead, 3.5 GB; the row-major gather 4.6 GB.
+// Bound: bytes that miss the L2, at the rate of a copy.  Measured with 64 FP32 columns at
+// L = 24 (n = 2,704,156, 692 MB per vector): the tiles fetch 1.72 GB per apply1, 2.5
+// times the gathered vector, in 558 us (with the 0.72 GB written 4.4 TB/s; a copy reaches
+// 4.9).  In row order they fetch 2.07 GB (590 us); dealt out in a fixed stride, where
+// workgroups with small tiles run ahead, 3.5 GB; the row-major gather 4.6 GB.  Fewer or
+// larger workgroups in flight (4 of 256, 4 of 512 threads per CU) and blocks of q = 11 or
+// 10 are slower (590 and 553, 600 and 700 us; the second apply 710 and 771, 735 and
+// 852 against 662), eight loads of the high half at once give nothing.
 template <class T, int EPI>
 __global__ __launch_bounds__(kPThreads) void k_panel(PanelArgs<T> a) {
   using V = typename PV<T>::type;
@@ -479,7 +483,8 @@ __global__ __launch_bounds__(kPThreads) void k_panel_fin(const double* __restric
 // ---- tables ------------------------------------------------------------------
 
 struct PanelTabArgs {
-  int L, k, Lh;
+  int L, k, Lh, ntiles;
+  const int* order;  // high configuration of each tile
   double zz4;
   double h[kMaxL];
   const uint32_t* pascal;
@@ -512,8 +517,8 @@ __device__ inline int block_row(const PanelTabArgs& a, uint32_t hi, int kl) {
   return row;
 }
 
-// One thread per low configuration and one per high configuration.  A high
-// configuration with no rows in the sector is a tile of no rows.
+// One thread per low configuration and one per tile, which is a high configuration that
+// has rows in the sector.
 __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
   const uint32_t id = blockIdx.x * 256 + threadIdx.x;
   const uint32_t* C = a.pascal;
@@ -544,31 +549,69 @@ __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
     int nd;
     a.lo_E[at + u] = half_energy(a, 0, kPanelQ, v, &nd);
   }
-  if (id < (1u << a.Lh)) {
-    const uint32_t v = id;
+  if (id < (uint32_t)a.ntiles) {
+    const uint32_t v = (uint32_t)a.order[id];
     const int kl = a.k - __popc(v);
     PanelTile t{};
-    if (kl >= 0 && kl <= kPanelQ) {
-      t.row0 = block_row(a, v, kl);
-      t.nrows = binom(kPanelQ, kl);
-      for (int c = 0; c < kl; ++c) t.aux += binom(kPanelQ, c);
-      t.E = half_energy(a, kPanelQ, a.Lh, v, &t.nd);
-      for (int b = 0; b + 1 < a.Lh; ++b)
-        if (((v >> b) ^ (v >> (b + 1))) & 1u)
-          t.off[t.cnt++] = block_row(a, v ^ (3u << b), kl) - t.row0;
-      // middle bond: even hi, the rows with the top low site up (the last
-      // C(11, kl - 1)) land on the first rows of hi | 1; odd hi, the rows with that
-      // site down land on the last rows of hi & ~1
-      const uint32_t pv = v ^ 1u;
-      const int pkl = a.k - __popc(pv), split = binom(kPanelQ - 1, kl);
-      if (pkl >= 0 && pkl <= kPanelQ) {
-        const int prow = block_row(a, pv, pkl);
-        t.mlo = (v & 1u) ? 0 : split;
-        t.mhi = (v & 1u) ? split : t.nrows;
-        t.mbase = (v & 1u) ? prow + binom(kPanelQ - 1, kl + 1) : prow - split;
-      }
+    t.row0 = block_row(a, v, kl);
+    t.nrows = binom(kPanelQ, kl);
+    for (int c = 0; c < kl; ++c) t.aux += binom(kPanelQ, c);
+    t.E = half_energy(a, kPanelQ, a.Lh, v, &t.nd);
+    for (int b = 0; b + 1 < a.Lh; ++b)
+      if (((v >> b) ^ (v >> (b + 1))) & 1u)
+        t.off[t.cnt++] = block_row(a, v ^ (3u << b), kl) - t.row0;
+    // middle bond: even hi, the rows with the top low site up (the last
+    // C(11, kl - 1)) land on the first rows of hi | 1; odd hi, the rows with that
+    // site down land on the last rows of hi & ~1
+    const uint32_t pv = v ^ 1u;
+    const int pkl = a.k - __popc(pv), split = binom(kPanelQ - 1, kl);
+    if (pkl >= 0 && pkl <= kPanelQ) {
+      const int prow = block_row(a, pv, pkl);
+      t.mlo = (v & 1u) ? 0 : split;
+      t.mhi = (v & 1u) ? split : t.nrows;
+      t.mbase = (v & 1u) ? prow + binom(kPanelQ - 1, kl + 1) : prow - split;
     }
-    a.tiles[v] = t;
+    a.tiles[id] = t;
+  }
+}
+
+// The order in which the tiles are taken: by the up spins of hi without its lowest site,
+// within that by the sum of their positions.  A flip inside that part keeps the first
+// and moves the second by one, and the flips at its lower end (the middle bond, the
+// lowest bond of hi) change the lowest site or go one group on: what a run of tiles
+// gathers lies in the groups next to it, where in row order the flips of the highest
+// sites go far.  An LRU cache of an XCD's L2 (262144 rows of 16 bytes) that sees the
+// tiles in this order fetches each vector 1.46 times at L = 24, in row order 3.01.
+// The card, where 256 tiles of an XCD are in flight at once, goes from 3.0 to 2.5; the two
+// applies of a step at L = 26 (64 FP32 columns) from 5.45 to 5.05 ms.
+void tile_order(Ham& H, int Lh) {
+  PanelTables& P = H.panel;
+  auto key = [&](uint32_t v) {
+    int pos = 0;
+    for (uint32_t w = v >> 1; w; w &= w - 1) pos += __builtin_ctz(w);
+    return (__builtin_popcount(v >> 1) << 8) + pos;  // pos <= 14 * 15 / 2
+  };
+  std::vector<int> count(kMaxHigh << 8, 0);
+  auto rows = [&](uint32_t v) -> int64_t {
+    const int kl = H.nup - __builtin_popcount(v);
+    return kl < 0 || kl > kPanelQ ? 0 : H.pascal_host[kPanelQ * kPascal + kl];
+  };
+  for (uint32_t v = 0; v < (1u << Lh); ++v)
+    if (rows(v)) ++count[key(v)];
+  int at = 0;
+  for (int& c : count) {
+    const int k = c;
+    c = at;
+    at += k;
+  }
+  P.order.resize(at);
+  for (uint32_t v = 0; v < (1u << Lh); ++v)
+    if (rows(v)) P.order[count[key(v)]++] = (int)v;
+  P.rows.resize(at);
+  int64_t before = 0;
+  for (int t = 0; t < at; ++t) {
+    P.rows[t] = before;
+    before += rows((uint32_t)P.order[t]);
   }
 }
 
@@ -581,13 +624,18 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   // upper limit: 32-bit byte offsets within a panel.
   P.ok = Lh >= 2 && Lh <= kMaxHigh && H.n > kPanelMinRows && H.n < (1ll << 28);
   if (!P.ok) return;
-  P.ntiles = 1 << Lh;
+  tile_order(H, Lh);
+  P.ntiles = (int)P.order.size();
   const size_t nt = P.ntiles * sizeof(PanelTile), nl = (size_t)1 << kPanelQ;
-  H.table(P.buf, nl * (sizeof(uint4) + sizeof(double)) + nt, s);
+  H.table(P.buf, nl * (sizeof(uint4) + sizeof(double)) + nt + P.ntiles * sizeof(int), s);
   P.lo_tab = P.buf.as<uint4>();
   P.lo_E = reinterpret_cast<double*>(P.lo_tab + nl);
   P.tiles = reinterpret_cast<PanelTile*>(P.lo_E + nl);
+  int* order = reinterpret_cast<int*>(P.tiles + P.ntiles);
+  MBL_HIP(hipMemcpyAsync(order, P.order.data(), P.ntiles * sizeof(int), hipMemcpyHostToDevice, s));
   PanelTabArgs a{};
+  a.order = order;
+  a.ntiles = P.ntiles;
   a.L = H.L;
   a.k = H.nup;
   a.Lh = Lh;
@@ -597,7 +645,7 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   a.tiles = P.tiles;
   a.lo_tab = P.lo_tab;
   a.lo_E = P.lo_E;
-  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)(std::max<size_t>(nl, P.ntiles) / 256)),
+  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)((std::max<size_t>(nl, P.ntiles) + 255) / 256)),
                      dim3(256), 0, s, a);
   MBL_CHECK_LAUNCH();
 }
@@ -613,30 +661,19 @@ namespace {
 // and 1.88 ms with 3, 4, 6 and 8; at L = 20 (64 FP64 columns) 245, 228, 217, 217 us.
 constexpr int kPanelPerCu = 8;
 
-// High configuration of a row: greedy unranking in colex order.
-int tile_of_row(const Ham& H, int64_t row) {
-  uint32_t hi = 0;
-  int p = H.L - 1;
-  for (int t = H.nup; t >= 1 && p >= kPanelQ; --t, --p) {
-    while (p >= kPanelQ && (int64_t)H.pascal_host[p * kPascal + t] > row) --p;
-    if (p < kPanelQ) break;
-    hi |= 1u << (p - kPanelQ);
-    row -= H.pascal_host[p * kPascal + t];
-  }
-  return (int)hi;
-}
-
 PanelSched panel_sched(const Ham& H, int npan) {
   PanelSched t{};
   t.ntiles = H.panel.ntiles;
   int most = 1;
+  const std::vector<int64_t>& rows = H.panel.rows;
   for (int x = 0; x <= 8; ++x) {
     const int64_t target = (int64_t)x * H.n * npan / 8;  // rows of all panels before XCD x
     const int64_t panel = target / H.n;
-    t.first[x] = (int)(panel * t.ntiles) + (panel < npan ? tile_of_row(H, target - panel * H.n) : 0);
+    t.first[x] = (int)(panel * t.ntiles) +
+                 (int)(std::lower_bound(rows.begin(), rows.end(), target - panel * H.n) -
+                       rows.begin());
     if (x) most = std::max(most, t.first[x] - t.first[x - 1]);
   }
-  t.first[0] = 0;  // tiles of no rows before the first row included
   t.nwg = 8 * std::min(most, 32 * kPanelPerCu);
   return t;
 }

@@ -155,8 +155,10 @@ struct PanelTile {
 struct PanelTables {
   bool ok = false;
   int ntiles = 0;
+  std::vector<int> order;     // high configuration of tile t
+  std::vector<int64_t> rows;  // rows of the tiles before tile t
   DevBuf buf;                // holds the three tables below
-  PanelTile* tiles = nullptr;  // by high configuration, which is row order
+  PanelTile* tiles = nullptr;  // in the order of `order`
   uint4* lo_tab = nullptr;     // per low configuration (k_panel_tables)
   double* lo_E = nullptr;
 };
