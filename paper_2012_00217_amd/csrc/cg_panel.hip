@@ -43,6 +43,7 @@ constexpr int kPWaves = kPThreads / 64;
 constexpr int kPanelQ = 12;       // low half: blocks of at most 924 rows
 constexpr int kPanelRows = 924;
 constexpr int kPanelMinRows = 13312;
+constexpr int kPanelMeanRows = 256;  // of a tile
 constexpr int kMaxHigh = 16;      // longest high half (L = 28)
 
 template <class T>
@@ -626,6 +627,13 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   if (!P.ok) return;
   tile_order(H, Lh);
   P.ntiles = (int)P.order.size();
+  // Sectors far from half filling have many tiles of few rows, which leave most lanes of a
+  // workgroup idle.  CG against the gather kernels, 32 FP64 columns, by rows per tile: 27
+  // (L = 24, 5 up) 1373 us for 657, 105 (7 up) 3010 for 2852, 157 (L = 20, 6 up) 675 for
+  // 619, 194 (L = 24, 8 up; 4 columns) 1514 for 1375; 304 (L = 20, 7 up) 842 for 887,
+  // 325 (L = 24, 9 up) 8006 for 10938.  Half filling has 600 to 800.
+  P.ok = H.n >= kPanelMeanRows * (int64_t)P.ntiles;
+  if (!P.ok) return;
   const size_t nt = P.ntiles * sizeof(PanelTile), nl = (size_t)1 << kPanelQ;
   H.table(P.buf, nl * (sizeof(uint4) + sizeof(double)) + nt + P.ntiles * sizeof(int), s);
   P.lo_tab = P.buf.as<uint4>();

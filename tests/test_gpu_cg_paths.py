@@ -104,3 +104,15 @@ def test_panel_cg_at_the_longest_chains(L, b, dtype, monkeypatch):
     assert err.max().item() <= (1e-12 if dtype == torch.float64 else 2e-5)
     del W, W0, R
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("L,nup", [(24, 5), (20, 6)])
+def test_sparse_sectors_keep_the_gather_kernels(L, nup, monkeypatch):
+    """Far from half filling the blocks of rows are short: the same kernels as with a launch
+    schedule asked for (here that of the default), to the bit."""
+    H = api.Hamiltonian(L, workloads.disorder(L, 4.0, 1), Sz=nup - 0.5 * L)
+    g = torch.Generator().manual_seed(5)
+    R = torch.randn(H.n, 6, generator=g, dtype=torch.float64).to(DEV)
+    W = H.pcg(R, 0.1, 5)
+    monkeypatch.setenv("MBL_APPLY_LANE_BYTES", "64")
+    assert torch.equal(W, H.pcg(R, 0.1, 5))
