@@ -750,12 +750,22 @@ ApplyArgs<T> base_args(const Ham& H, double sigma) {
 
 }  // namespace
 
+// A launch schedule or the two-pass kernels asked for through the environment
+// concern the gather kernels: the CG then runs on those.
+bool gather_forced() {
+  for (const char* v : {"MBL_APPLY_CHUNK_BYTES", "MBL_APPLY_LANE_BYTES", "MBL_APPLY_XCD_GROUP",
+                        "MBL_APPLY_SLOTS_PER_XCD"})
+    if (std::getenv(v)) return true;
+  return env_int("MBL_APPLY_SPLIT", 0) != 0;
+}
+
 template <class T>
 void launch_apply(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int64_t ldy, int w,
                   hipStream_t s) {
   if (H.n == 0 || w == 0) return;
   PhaseTick tick(PhaseClock::APPLY, s);
   if (split_apply<T>(H, sigma, X, ldx, Y, ldy, w, s)) return;
+  if (!gather_forced() && tile_apply<T>(H, sigma, X, ldx, Y, ldy, w, s)) return;
   const bool aligned = al16(X, ldx, sizeof(T)) && al16(Y, ldy, sizeof(T));
   ApplyArgs<T> a = base_args<T>(H, sigma);
   a.X = X;
@@ -1170,15 +1180,6 @@ void fuse_call(CgFuser& f, const std::vector<int64_t>& key, Job& job, hipStream_
   lk.unlock();
   if (tk.err) std::rethrow_exception(tk.err);
   MBL_HIP(hipStreamWaitEvent(s, tk.finished, 0));
-}
-
-// A launch schedule or the two-pass kernels asked for through the environment
-// concern the gather kernels: the CG then runs on those.
-bool gather_forced() {
-  for (const char* v : {"MBL_APPLY_CHUNK_BYTES", "MBL_APPLY_LANE_BYTES", "MBL_APPLY_XCD_GROUP",
-                        "MBL_APPLY_SLOTS_PER_XCD"})
-    if (std::getenv(v)) return true;
-  return env_int("MBL_APPLY_SPLIT", 0) != 0;
 }
 
 template <class T>

@@ -44,7 +44,8 @@ constexpr int kPanelQ = 12;       // low half: blocks of at most 924 rows
 constexpr int kPanelRows = 924;
 constexpr int kPanelMinRows = 13312;
 constexpr int kPanelMeanRows = 256;  // of a tile
-constexpr int kMaxHigh = 16;      // longest high half (L = 28)
+constexpr int kPanelMaxHigh = 16;  // longest high half (L = 28)
+constexpr int kMaxHigh = 18;       // of the apply's tiles (L = 28)
 
 template <class T>
 struct PV;
@@ -55,12 +56,6 @@ struct PV<double> {
 template <>
 struct PV<float> {
   typedef float type __attribute__((ext_vector_type(4)));
-};
-
-// Tiles of XCD x: linear indices [first[x], first[x + 1]) of panel * ntiles + tile.
-struct PanelSched {
-  int first[9];
-  int ntiles, nwg;
 };
 
 template <class T>
@@ -87,9 +82,6 @@ __device__ inline typename PV<T>::type pload(const T* base, uint32_t off) {
   if constexpr (kNt) return __builtin_nontemporal_load(p);
   return *p;
 }
-
-// The tile descriptors are read-only and the same in every lane: scalar loads.
-#define MBL_CONST __attribute__((address_space(4)))
 
 // Sum over the wavefront of VE values per lane.  Lanes that differ in the low
 // log2(VE) bits first share out the columns (each keeps half of its values and
@@ -484,8 +476,7 @@ __global__ __launch_bounds__(kPThreads) void k_panel_fin(const double* __restric
 // ---- tables ------------------------------------------------------------------
 
 struct PanelTabArgs {
-  int L, k, Lh, ntiles;
-  const int* order;  // high configuration of each tile
+  int L, k, q, Lh;  // q low sites, Lh high sites
   double zz4;
   double h[kMaxL];
   const uint32_t* pascal;
@@ -514,29 +505,79 @@ __device__ inline double half_energy(const PanelTabArgs& a, int base, int len, u
 __device__ inline int block_row(const PanelTabArgs& a, uint32_t hi, int kl) {
   int row = 0, j = 0;
   for (int p = 0; p < a.Lh; ++p)
-    if ((hi >> p) & 1u) row += (int)a.pascal[(kPanelQ + p) * kPascal + kl + ++j];
+    if ((hi >> p) & 1u) row += (int)a.pascal[(a.q + p) * kPascal + kl + ++j];
   return row;
 }
 
-// One thread per low configuration and one per tile, which is a high configuration that
-// has rows in the sector.
+// Subsets of {0 .. m - 1} with c elements and sum s, and those with a smaller sum.
+constexpr int kMaxSum = 17 * 16 / 2;
+struct Subsets {
+  uint16_t n[kMaxHigh][kMaxHigh][kMaxSum + 1], below[kMaxHigh][kMaxHigh][kMaxSum + 1];
+  constexpr Subsets() : n(), below() {
+    n[0][0][0] = 1;
+    for (int m = 1; m < kMaxHigh; ++m)
+      for (int c = 0; c < kMaxHigh; ++c)
+        for (int t = 0; t <= kMaxSum; ++t)
+          n[m][c][t] = (uint16_t)(n[m - 1][c][t] +
+                                  (c > 0 && t >= m - 1 ? n[m - 1][c - 1][t - (m - 1)] : 0));
+    for (int m = 0; m < kMaxHigh; ++m)
+      for (int c = 0; c < kMaxHigh; ++c)
+        for (int t = 1; t <= kMaxSum; ++t)
+          below[m][c][t] = (uint16_t)(below[m][c][t - 1] + n[m][c][t - 1]);
+  }
+};
+__device__ const Subsets kSubsets = Subsets();
+
+// The order in which the tiles are taken: by the up spins of hi without its lowest site,
+// within that by the sum of their positions.  A flip inside that part keeps the first
+// and moves the second by one, and the flips at its lower end (the middle bond, the
+// lowest bond of hi) change the lowest site or go one group on: what a run of tiles
+// gathers lies in the groups next to it, where in row order the flips of the highest
+// sites go far.  An LRU cache of an XCD's L2 (262144 rows of 16 bytes) that sees the
+// tiles in this order fetches each vector 1.46 times at L = 24, in row order 3.01.
+// The card, where 256 tiles of an XCD are in flight at once, goes from 3.0 to 2.5; the two
+// applies of a step at L = 26 (64 FP32 columns) from 5.45 to 5.05 ms.
+//
+// The two values of the lowest site follow each other, so a group of tiles is a number of
+// equal pairs (where both have rows) and the first tile of a row count is a division
+// (first_tile).
+__device__ inline int tile_rank(const PanelTabArgs& a, uint32_t hi) {
+  auto rows = [&](int kl) { return kl < 0 || kl > a.q ? 0 : (int)a.pascal[a.q * kPascal + kl]; };
+  const int m = a.Lh - 1;
+  int c = __popc(hi >> 1), sum = 0, t = 0;
+  for (uint32_t w = hi >> 1; w; w &= w - 1) sum += __ffs(w) - 1;
+  for (int g = 0; g < c; ++g)
+    t += (int)a.pascal[m * kPascal + g] * ((rows(a.k - g) > 0) + (rows(a.k - g - 1) > 0));
+  const int even = rows(a.k - c) > 0, odd = rows(a.k - c - 1) > 0;
+  int i = kSubsets.below[m][c][sum];
+  for (int b = m - 1; b >= 0; --b)
+    if ((hi >> (b + 1)) & 1u) {
+      i += kSubsets.n[b][c][sum];
+      --c;
+      sum -= b;
+    }
+  return t + i * (even + odd) + ((hi & 1u) ? even : 0);
+}
+
+// One thread per low configuration and one per high configuration; a tile is one of those
+// that have rows in the sector.
 __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
   const uint32_t id = blockIdx.x * 256 + threadIdx.x;
   const uint32_t* C = a.pascal;
   auto binom = [&](int i, int t) { return t < 0 || t > i ? 0 : (int)C[i * kPascal + t]; };
-  if (id < (1u << kPanelQ)) {
+  if (id < (1u << a.q)) {
     // by (up spins, value); the flips as rows of the LDS tile (row u at u + 1,
     // the zero row at 0), 10 bits each, three to a word, and their number in the
     // top 4 bits of the last word
     const uint32_t v = id;
     const int kl = __popc(v);
     int at = 0, u = 0, j = 0;
-    for (int c = 0; c < kl; ++c) at += binom(kPanelQ, c);
-    for (int p = 0; p < kPanelQ; ++p)
+    for (int c = 0; c < kl; ++c) at += binom(a.q, c);
+    for (int p = 0; p < a.q; ++p)
       if ((v >> p) & 1u) u += binom(p, ++j);
     uint32_t w[4] = {0, 0, 0, 0};
     int m = 0;
-    for (int b = 0; b + 1 < kPanelQ; ++b) {
+    for (int b = 0; b + 1 < a.q; ++b) {
       if (!(((v >> b) ^ (v >> (b + 1))) & 1u)) continue;
       const int c = binom(b, __popc(v & ((1u << b) - 1u)));
       const uint32_t f = (uint32_t)(u + (((v >> b) & 1u) ? c : -c) + 1) << (10 * (m % 3));
@@ -548,16 +589,17 @@ __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
     }
     a.lo_tab[at + u] = make_uint4(w[0], w[1], w[2], w[3] | ((uint32_t)m << 28));
     int nd;
-    a.lo_E[at + u] = half_energy(a, 0, kPanelQ, v, &nd);
+    a.lo_E[at + u] = half_energy(a, 0, a.q, v, &nd);
   }
-  if (id < (uint32_t)a.ntiles) {
-    const uint32_t v = (uint32_t)a.order[id];
+  if (id < (1u << a.Lh)) {
+    const uint32_t v = id;
     const int kl = a.k - __popc(v);
+    if (kl < 0 || kl > a.q) return;
     PanelTile t{};
     t.row0 = block_row(a, v, kl);
-    t.nrows = binom(kPanelQ, kl);
-    for (int c = 0; c < kl; ++c) t.aux += binom(kPanelQ, c);
-    t.E = half_energy(a, kPanelQ, a.Lh, v, &t.nd);
+    t.nrows = binom(a.q, kl);
+    for (int c = 0; c < kl; ++c) t.aux += binom(a.q, c);
+    t.E = half_energy(a, a.q, a.Lh, v, &t.nd);
     for (int b = 0; b + 1 < a.Lh; ++b)
       if (((v >> b) ^ (v >> (b + 1))) & 1u)
         t.off[t.cnt++] = block_row(a, v ^ (3u << b), kl) - t.row0;
@@ -565,87 +607,61 @@ __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
     // C(11, kl - 1)) land on the first rows of hi | 1; odd hi, the rows with that
     // site down land on the last rows of hi & ~1
     const uint32_t pv = v ^ 1u;
-    const int pkl = a.k - __popc(pv), split = binom(kPanelQ - 1, kl);
-    if (pkl >= 0 && pkl <= kPanelQ) {
+    const int pkl = a.k - __popc(pv), split = binom(a.q - 1, kl);
+    if (pkl >= 0 && pkl <= a.q) {
       const int prow = block_row(a, pv, pkl);
       t.mlo = (v & 1u) ? 0 : split;
       t.mhi = (v & 1u) ? split : t.nrows;
-      t.mbase = (v & 1u) ? prow + binom(kPanelQ - 1, kl + 1) : prow - split;
+      t.mbase = (v & 1u) ? prow + binom(a.q - 1, kl + 1) : prow - split;
     }
-    a.tiles[id] = t;
+    a.tiles[tile_rank(a, v)] = t;
   }
 }
 
-// The order in which the tiles are taken: by the up spins of hi without its lowest site,
-// within that by the sum of their positions.  A flip inside that part keeps the first
-// and moves the second by one, and the flips at its lower end (the middle bond, the
-// lowest bond of hi) change the lowest site or go one group on: what a run of tiles
-// gathers lies in the groups next to it, where in row order the flips of the highest
-// sites go far.  An LRU cache of an XCD's L2 (262144 rows of 16 bytes) that sees the
-// tiles in this order fetches each vector 1.46 times at L = 24, in row order 3.01.
-// The card, where 256 tiles of an XCD are in flight at once, goes from 3.0 to 2.5; the two
-// applies of a step at L = 26 (64 FP32 columns) from 5.45 to 5.05 ms.
-void tile_order(Ham& H, int Lh) {
-  PanelTables& P = H.panel;
-  auto key = [&](uint32_t v) {
-    int pos = 0;
-    for (uint32_t w = v >> 1; w; w &= w - 1) pos += __builtin_ctz(w);
-    return (__builtin_popcount(v >> 1) << 8) + pos;  // pos <= 14 * 15 / 2
+// Calls f(tiles per pair, rows of the first, rows of both, pairs) for every group.
+template <class F>
+void tile_groups(const Ham& H, int q, F f) {
+  const int m = H.L - q - 1;
+  auto rows = [&](int kl) -> int64_t {
+    return kl < 0 || kl > q ? 0 : H.pascal_host[q * kPascal + kl];
   };
-  std::vector<int> count(kMaxHigh << 8, 0);
-  auto rows = [&](uint32_t v) -> int64_t {
-    const int kl = H.nup - __builtin_popcount(v);
-    return kl < 0 || kl > kPanelQ ? 0 : H.pascal_host[kPanelQ * kPascal + kl];
-  };
-  for (uint32_t v = 0; v < (1u << Lh); ++v)
-    if (rows(v)) ++count[key(v)];
-  int at = 0;
-  for (int& c : count) {
-    const int k = c;
-    c = at;
-    at += k;
-  }
-  P.order.resize(at);
-  for (uint32_t v = 0; v < (1u << Lh); ++v)
-    if (rows(v)) P.order[count[key(v)]++] = (int)v;
-  P.rows.resize(at);
-  int64_t before = 0;
-  for (int t = 0; t < at; ++t) {
-    P.rows[t] = before;
-    before += rows((uint32_t)P.order[t]);
+  for (int c = 0; c <= m; ++c) {
+    const int64_t even = rows(H.nup - c), odd = rows(H.nup - c - 1);
+    if (even + odd == 0) continue;
+    f((even > 0) + (odd > 0), even > 0 ? even : odd, even + odd,
+      (int64_t)H.pascal_host[m * kPascal + c]);
   }
 }
 
-}  // namespace
+// Tiles before the first one that has `row` or more rows before it.
+int first_tile(const Ham& H, const PanelTables& P, int64_t row) {
+  int64_t t = 0;
+  tile_groups(H, P.q, [&](int per, int64_t first, int64_t both, int64_t pairs) {
+    const int64_t i = std::min(pairs, row / both), rest = row - i * both;
+    t += i * per;
+    row = i == pairs ? rest : 0;
+    if (i < pairs && rest > 0) t += rest <= first ? 1 : per;
+  });
+  return (int)t;
+}
 
-void build_panel_tables(Ham& H, hipStream_t s) {
-  PanelTables& P = H.panel;
-  const int Lh = H.L - kPanelQ;
-  // Smaller sectors are bound by launches, of which this path has as many.  The
-  // upper limit: 32-bit byte offsets within a panel.
-  P.ok = Lh >= 2 && Lh <= kMaxHigh && H.n > kPanelMinRows && H.n < (1ll << 28);
-  if (!P.ok) return;
-  tile_order(H, Lh);
-  P.ntiles = (int)P.order.size();
-  // Sectors far from half filling have many tiles of few rows, which leave most lanes of a
-  // workgroup idle.  CG against the gather kernels, 32 FP64 columns, by rows per tile: 27
-  // (L = 24, 5 up) 1373 us for 657, 105 (7 up) 3010 for 2852, 157 (L = 20, 6 up) 675 for
-  // 619, 194 (L = 24, 8 up; 4 columns) 1514 for 1375; 304 (L = 20, 7 up) 842 for 887,
-  // 325 (L = 24, 9 up) 8006 for 10938.  Half filling has 600 to 800.
-  P.ok = H.n >= kPanelMeanRows * (int64_t)P.ntiles;
-  if (!P.ok) return;
-  const size_t nt = P.ntiles * sizeof(PanelTile), nl = (size_t)1 << kPanelQ;
-  H.table(P.buf, nl * (sizeof(uint4) + sizeof(double)) + nt + P.ntiles * sizeof(int), s);
+// The tables of P for blocks of q low sites; none where the mean block is short.
+void build_tables_of(Ham& H, PanelTables& P, int q, int mean_rows, hipStream_t s) {
+  const int Lh = H.L - q;
+  int64_t tiles = 0;
+  tile_groups(H, q, [&](int per, int64_t, int64_t, int64_t pairs) { tiles += per * pairs; });
+  if (H.n < mean_rows * tiles) return;
+  P.q = q;
+  P.ntiles = (int)tiles;
+  const size_t nt = P.ntiles * sizeof(PanelTile), nl = (size_t)1 << q;
+  H.table(P.buf, nl * (sizeof(uint4) + sizeof(double)) + nt, s);
   P.lo_tab = P.buf.as<uint4>();
   P.lo_E = reinterpret_cast<double*>(P.lo_tab + nl);
   P.tiles = reinterpret_cast<PanelTile*>(P.lo_E + nl);
-  int* order = reinterpret_cast<int*>(P.tiles + P.ntiles);
-  MBL_HIP(hipMemcpyAsync(order, P.order.data(), P.ntiles * sizeof(int), hipMemcpyHostToDevice, s));
   PanelTabArgs a{};
-  a.order = order;
-  a.ntiles = P.ntiles;
   a.L = H.L;
   a.k = H.nup;
+  a.q = q;
   a.Lh = Lh;
   a.zz4 = 0.25 * H.J * H.Delta;
   std::copy(H.h, H.h + kMaxL, a.h);
@@ -653,9 +669,32 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   a.tiles = P.tiles;
   a.lo_tab = P.lo_tab;
   a.lo_E = P.lo_E;
-  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)((std::max<size_t>(nl, P.ntiles) + 255) / 256)),
-                     dim3(256), 0, s, a);
+  const size_t threads = std::max<size_t>(nl, (size_t)1 << Lh);
+  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);
   MBL_CHECK_LAUNCH();
+  P.ok = true;
+}
+
+}  // namespace
+
+void build_panel_tables(Ham& H, hipStream_t s) {
+  auto fits = [&](int q, int most_high, int64_t least) {
+    return H.L - q >= 2 && H.L - q <= most_high && H.n > least;
+  };
+  // Panels: smaller sectors are bound by launches, of which this path has as many.  The
+  // upper limit: 32-bit byte offsets within a panel.
+  //
+  // Mean rows: sectors far from half filling have many tiles of few rows, which leave
+  // most lanes of a workgroup idle.  CG against the gather kernels, 32 FP64 columns, by
+  // rows per tile: 27 (L = 24, 5 up) 1373 us for 657, 105 (7 up) 3010 for 2852, 157
+  // (L = 20, 6 up) 675 for 619, 194 (L = 24, 8 up; 4 columns) 1514 for 1375; 304 (L = 20,
+  // 7 up) 842 for 887, 325 (L = 24, 9 up) 8006 for 10938.  Half filling has 600 to 800.
+  // The apply: 35 153 for 75, 57 225 for 175, 88 (L = 24, 9 up) 419 for 365; 103 (L = 21,
+  // 8 up; 64 columns) 69 for 82, 123 (L = 24, 10 up) 555 for 604.  Half filling has 150 to
+  // 230.
+  if (!H.col_ok && fits(kPanelQ, kPanelMaxHigh, kPanelMinRows) && H.n < (1ll << 28))
+    build_tables_of(H, H.panel, kPanelQ, kPanelMeanRows, s);
+  if (fits(kTileQ, kMaxHigh, kTileMinRows)) build_tables_of(H, H.tile, kTileQ, kTileMeanRows, s);
 }
 
 bool panel_usable(const Ham& H, int b) {
@@ -669,24 +708,22 @@ namespace {
 // and 1.88 ms with 3, 4, 6 and 8; at L = 20 (64 FP64 columns) 245, 228, 217, 217 us.
 constexpr int kPanelPerCu = 8;
 
-PanelSched panel_sched(const Ham& H, int npan) {
+}  // namespace
+
+PanelSched panel_sched(const Ham& H, const PanelTables& P, int npan, int slots) {
+  const int64_t n = H.n;
   PanelSched t{};
-  t.ntiles = H.panel.ntiles;
+  t.ntiles = P.ntiles;
   int most = 1;
-  const std::vector<int64_t>& rows = H.panel.rows;
   for (int x = 0; x <= 8; ++x) {
-    const int64_t target = (int64_t)x * H.n * npan / 8;  // rows of all panels before XCD x
-    const int64_t panel = target / H.n;
-    t.first[x] = (int)(panel * t.ntiles) +
-                 (int)(std::lower_bound(rows.begin(), rows.end(), target - panel * H.n) -
-                       rows.begin());
+    const int64_t target = (int64_t)x * n * npan / 8;  // rows of all panels before XCD x
+    const int64_t panel = target / n;
+    t.first[x] = (int)(panel * t.ntiles) + first_tile(H, P, target - panel * n);
     if (x) most = std::max(most, t.first[x] - t.first[x - 1]);
   }
-  t.nwg = 8 * std::min(most, 32 * kPanelPerCu);
+  t.nwg = 8 * std::min(most, slots);
   return t;
 }
-
-}  // namespace
 
 template <class T>
 void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W,
@@ -745,7 +782,7 @@ void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t
 
   // CG steps [from, to) on the leading np panels; columns from `cols` on are frozen
   auto steps = [&](int np, int cols, int from, int to) {
-    const PanelSched ts = panel_sched(H, np);
+    const PanelSched ts = panel_sched(H, P, np, 32 * kPanelPerCu);
     PanelArgs<T> a1{};
     a1.tiles = P.tiles;
     a1.lo_tab = P.lo_tab;

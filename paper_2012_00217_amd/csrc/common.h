@@ -148,20 +148,34 @@ struct PanelTile {
   int32_t mlo, mhi, mbase;  // middle bond: rows [mlo, mhi) map to rows mbase + u
   int32_t cnt;              // anti-aligned bonds of hi: row u maps to row0 + off + u
   double E;                 // energy of hi
-  int32_t off[16];
+  int32_t off[18];
 };
 
 // Tables of the panel CG, built once per sector.
 struct PanelTables {
   bool ok = false;
-  int ntiles = 0;
-  std::vector<int> order;     // high configuration of tile t
-  std::vector<int64_t> rows;  // rows of the tiles before tile t
+  int q = 0, ntiles = 0;
   DevBuf buf;                // holds the three tables below
-  PanelTile* tiles = nullptr;  // in the order of `order`
+  PanelTile* tiles = nullptr;  // in the order of tile_rank
   uint4* lo_tab = nullptr;     // per low configuration (k_panel_tables)
   double* lo_E = nullptr;
 };
+
+// Tiles of XCD x: linear indices [first[x], first[x + 1]) of panel * ntiles + tile.
+struct PanelSched {
+  int first[9];
+  int ntiles, nwg;
+};
+
+// The tile descriptors are read-only and the same in every lane: scalar loads.
+#define MBL_CONST __attribute__((address_space(4)))
+
+// Low half of the plain apply's tiles (apply_tile.hip).
+constexpr int kTileQ = 10;
+// L = 12 (924 rows) and up at half filling: 4.4 us an apply of 32 FP64 columns, k_apply 6.3;
+// shorter chains have no two high sites.
+constexpr int kTileMinRows = 512;
+constexpr int kTileMeanRows = 120;  // of a tile
 
 // Per-sector Hamiltonian data (the opaque mbl_ham).
 struct Ham {
@@ -175,7 +189,8 @@ struct Ham {
   DevBuf diag;     // double [n]  <s|H|s>
   std::vector<uint32_t> pascal_host;
   SplitTables split;
-  PanelTables panel;
+  PanelTables panel;  // of the panel CG
+  PanelTables tile;   // of the plain apply
   bool col_ok = false;  // the sector fits the one-workgroup-per-column CG
   DevBuf col_tab;       // its neighbour lists (cg_column.hip)
   // Stream the tables are allocated and freed on, stream-ordered (worker
@@ -321,6 +336,11 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
 // The same with panel-major CG vectors (cg_panel.hip), for sectors whose vectors
 // leave the caches; panel_usable: the sector has its tables.
 void build_panel_tables(Ham& H, hipStream_t s);
+PanelSched panel_sched(const Ham& H, const PanelTables& P, int npan, int slots);
+// Plain apply by blocks of rows; false: the sector or the block is not one for it.
+template <class T>
+bool tile_apply(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int64_t ldy, int w,
+                hipStream_t s);
 bool panel_usable(const Ham& H, int b);
 template <class T>
 void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W,

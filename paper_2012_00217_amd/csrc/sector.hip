@@ -126,7 +126,7 @@ void build_tables(Ham& H, hipStream_t s) {
                      H.diag.as<double>());
   MBL_CHECK_LAUNCH();
   build_column_tables(H, s);
-  if (!H.col_ok) build_panel_tables(H, s);
+  build_panel_tables(H, s);
 }
 
 void rank_states(const Ham& H, const uint64_t* q_dev, int64_t cnt, int64_t* out_dev,
