@@ -201,8 +201,8 @@ __global__ __launch_bounds__(256, 4) void k_gram(int64_t n, const T* __restrict_
 // (192 x 192, 170 splits: 17 us, now 7.8).
 // sym: elements below the diagonal are written as the mirror of those above.
 __global__ __launch_bounds__(256) void k_gram_fold(const double* __restrict__ part, int splits,
-                                                   int p, int q, int sym, double* __restrict__ C,
-                                                   int64_t ldc) {
+                                                   int p, int q, int sym, double scale,
+                                                   double* __restrict__ C, int64_t ldc) {
   __shared__ double sm[16][17];
   const int e = threadIdx.x & 15, g = threadIdx.x >> 4;
   const int64_t step = (int64_t)p * q, idx = (int64_t)blockIdx.x * 16 + e;
@@ -216,6 +216,7 @@ __global__ __launch_bounds__(256) void k_gram_fold(const double* __restrict__ pa
   __syncthreads();
   if (g != 0 || !mine) return;
   for (int k = 1; k < 16; ++k) s += sm[k][e];
+  s *= scale;
   C[r * ldc + c] = s;
   if (sym && r < c) C[c * ldc + r] = s;
 }
@@ -249,11 +250,12 @@ struct CombineStage {
 };
 
 template <class T, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* __restrict__ A, int64_t lda,
-                                                 int p, const double* __restrict__ Cm,
-                                                 int64_t ldc, T* __restrict__ Y, int64_t ldy,
-                                                 int q, double beta, int vec, int kc,
-                                                 int64_t tiles) {
+__global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* A, int64_t lda, int p,
+                                                     const double* __restrict__ Cm, int64_t ldc,
+                                                     T* Y, int64_t ldy, int q, double beta,
+                                                     double scale,
+                                                     const double* __restrict__ colscale, int vec,
+                                                     int kc, int64_t tiles) {
   using M = Mfma<T>;
   using S = CombineStage<T>;
   constexpr int VE = S::VE, SL = S::SL, GK = S::GK, W = 16 * NB;
@@ -298,8 +300,9 @@ __global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* __restr
         __syncthreads();  // the wavefronts are done with the chunk before
         for (int e = threadIdx.x; e < kc * W; e += 64 * NW) {
           const int k = e / W, c = e % W;
+          const double cscale = colscale && c0 + c < q ? scale * colscale[c0 + c] : scale;
           Cs[S::template at<W>(k, c)] =
-              (k0 + k < p && c0 + c < q) ? (T)Cm[(int64_t)(k0 + k) * ldc + c0 + c] : (T)0;
+              (k0 + k < p && c0 + c < q) ? (T)(Cm[(int64_t)(k0 + k) * ldc + c0 + c] * cscale) : (T)0;
         }
         __syncthreads();
       }
@@ -337,6 +340,22 @@ __global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* __restr
       }
     }
   }
+}
+
+// R = sign A - X diag(mu); A may be R.  The product is rounded before the sum, as in a
+// combination with diag(-mu).
+template <class T>
+__global__ __launch_bounds__(256) void k_residual(int64_t n, int b, const T* A, int64_t lda, T sign,
+                                                  const T* __restrict__ X, int64_t ldx,
+                                                  const double* __restrict__ mu, T* R,
+                                                  int64_t ldr) {
+#pragma clang fp contract(off)
+  const int64_t idx = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (idx >= n * b) return;
+  const int64_t r = idx / b;
+  const int c = (int)(idx % b);
+  const T t = X[r * ldx + c] * (T)-mu[c];
+  R[r * ldr + c] = sign * A[r * lda + c] + t;
 }
 
 template <class S, class D>
@@ -420,7 +439,8 @@ template GramPlan gram_plan<float>(int64_t, int, int, bool);
 
 template <class T>
 void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int p, const T* B,
-                      int64_t ldb, int q, double* C, int64_t ldc, double* part, hipStream_t s) {
+                      int64_t ldb, int q, double* C, int64_t ldc, double* part, hipStream_t s,
+                      double scale) {
   if (p == 0 || q == 0) return;
   PhaseTick tick(PhaseClock::GRAM, s);
   const uintptr_t align = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) |
@@ -431,17 +451,17 @@ void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int
                      s, n, A, lda, p, B, ldb, q, g.sym, vec, g.tiles, g.rows, part);
   MBL_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_gram_fold, dim3((unsigned)(((int64_t)p * q + 15) / 16)), dim3(256), 0, s,
-                     part, (int)g.splits, p, q, g.sym, C, ldc);
+                     part, (int)g.splits, p, q, g.sym, scale, C, ldc);
   MBL_CHECK_LAUNCH();
 }
 
 template <class T>
 void launch_gram(int64_t n, const T* A, int64_t lda, int p, const T* B, int64_t ldb, int q,
-                 double* C, int64_t ldc, hipStream_t s) {
+                 double* C, int64_t ldc, hipStream_t s, double scale) {
   if (p == 0 || q == 0) return;
   const GramPlan g = gram_plan<T>(n, p, q, A == B && lda == ldb);
   DevBuf part(g.part_bytes, s);
-  launch_gram_part<T>(g, n, A, lda, p, B, ldb, q, C, ldc, part.as<double>(), s);
+  launch_gram_part<T>(g, n, A, lda, p, B, ldb, q, C, ldc, part.as<double>(), s, scale);
 }
 
 // ---- Gram partials in a fixed device array -------------------------------
@@ -473,9 +493,12 @@ double* gram_scratch() {
   return g_scratch[dev];
 }
 
+bool combine_wide(int64_t n, int q) { return q > 32 && n >= 32768; }
+
 template <class T, int NB, int NW>
 void launch_combine_as(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc,
-                       T* Y, int64_t ldy, int q, double beta, hipStream_t s) {
+                       T* Y, int64_t ldy, int q, double beta, double scale, const double* colscale,
+                       hipStream_t s) {
   using S = CombineStage<T>;
   constexpr size_t kLds = 96 * 1024;  // p = 192 of 64 FP64 columns in one chunk
   constexpr int W = 16 * NB;
@@ -494,24 +517,38 @@ void launch_combine_as(int64_t n, const T* A, int64_t lda, int p, const double* 
     MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_combine<T, NB, NW>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL((k_combine<T, NB, NW>), dim3((unsigned)grid, (unsigned)cols), dim3(64 * NW),
-                     lds, s, n, A, lda, p, C, ldc, Y, ldy, q, beta, (align % 16) == 0 ? 1 : 0, kc,
-                     tiles);
+                     lds, s, n, A, lda, p, C, ldc, Y, ldy, q, beta, scale,
+                     colscale, (align % 16) == 0 ? 1 : 0, kc, tiles);
   MBL_CHECK_LAUNCH();
 }
 
 template <class T>
 void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc, T* Y,
-                    int64_t ldy, int q, double beta, hipStream_t s) {
+                    int64_t ldy, int q, double beta, hipStream_t s, double scale,
+                    const double* colscale) {
   if (n == 0 || q == 0) return;
   // Wide: all 64 columns in one wavefront read A once, and 16 wavefronts share a C of up to
   // 96 KB (192 -> 64 columns, n = 184756, FP64: 137 us, two blocks of 32 columns 150).
   // Narrow: no work on absent columns (51 -> 17, n = 705432: 115 us, wide 143), and for
   // short sectors less C per workgroup and more workgroups (96 -> 32, n = 3432: 13 us,
   // wide 23).
-  if (q > 32 && n >= 32768)
-    launch_combine_as<T, 4, 16>(n, A, lda, p, C, ldc, Y, ldy, q, beta, s);
+  if (combine_wide(n, q))
+    launch_combine_as<T, 4, 16>(n, A, lda, p, C, ldc, Y, ldy, q, beta, scale, colscale, s);
   else
-    launch_combine_as<T, 2, 8>(n, A, lda, p, C, ldc, Y, ldy, q, beta, s);
+    launch_combine_as<T, 2, 8>(n, A, lda, p, C, ldc, Y, ldy, q, beta, scale, colscale, s);
+}
+
+// One block of columns: a wavefront has read its 16 rows of A when it writes them, and no
+// other reads them (rows read ahead beyond the end are not used).
+bool combine_in_place(int64_t n, int q) { return q <= (combine_wide(n, q) ? 64 : 32); }
+
+template <class T>
+void launch_residual(int64_t n, int b, const T* A, int64_t lda, double sign, const T* X,
+                     int64_t ldx, const double* mu, T* R, int64_t ldr, hipStream_t s) {
+  if (n * b == 0) return;
+  hipLaunchKernelGGL(k_residual<T>, dim3(g1(n * b)), dim3(256), 0, s, n, b, A, lda, (T)sign, X, ldx,
+                     mu, R, ldr);
+  MBL_CHECK_LAUNCH();
 }
 
 template <class S, class D>
@@ -538,19 +575,25 @@ void launch_randn(int64_t n, int b, uint64_t seed, T* X, int64_t ldx, hipStream_
 }
 
 template void launch_gram<double>(int64_t, const double*, int64_t, int, const double*, int64_t,
-                                  int, double*, int64_t, hipStream_t);
+                                  int, double*, int64_t, hipStream_t, double);
 template void launch_gram<float>(int64_t, const float*, int64_t, int, const float*, int64_t, int,
-                                 double*, int64_t, hipStream_t);
+                                 double*, int64_t, hipStream_t, double);
 template void launch_gram_part<double>(const GramPlan&, int64_t, const double*, int64_t, int,
                                        const double*, int64_t, int, double*, int64_t, double*,
-                                       hipStream_t);
+                                       hipStream_t, double);
 template void launch_gram_part<float>(const GramPlan&, int64_t, const float*, int64_t, int,
                                       const float*, int64_t, int, double*, int64_t, double*,
-                                      hipStream_t);
+                                      hipStream_t, double);
 template void launch_combine<double>(int64_t, const double*, int64_t, int, const double*, int64_t,
-                                     double*, int64_t, int, double, hipStream_t);
+                                     double*, int64_t, int, double, hipStream_t, double,
+                                     const double*);
 template void launch_combine<float>(int64_t, const float*, int64_t, int, const double*, int64_t,
-                                    float*, int64_t, int, double, hipStream_t);
+                                    float*, int64_t, int, double, hipStream_t, double,
+                                    const double*);
+template void launch_residual<double>(int64_t, int, const double*, int64_t, double, const double*,
+                                      int64_t, const double*, double*, int64_t, hipStream_t);
+template void launch_residual<float>(int64_t, int, const float*, int64_t, double, const float*,
+                                     int64_t, const double*, float*, int64_t, hipStream_t);
 template void launch_convert<double, float>(int64_t, int, const double*, int64_t, float*, int64_t,
                                             hipStream_t);
 template void launch_convert<float, double>(int64_t, int, const float*, int64_t, double*, int64_t,

@@ -383,7 +383,7 @@ void launch_jacobi(const Ham& H, double sigma, T* out, hipStream_t s);
 // Gram C = A^T B (FP64 p x q, row-major ldc) with deterministic reduction.
 template <class T>
 void launch_gram(int64_t n, const T* A, int64_t lda, int p, const T* B, int64_t ldb, int q,
-                 double* C, int64_t ldc, hipStream_t s);
+                 double* C, int64_t ldc, hipStream_t s, double scale = 1.0);
 
 // Launch plan of the Gram: tiles x splits workgroups, each split's FP64
 // partial p x q tile in `part` (part_bytes).  The plan depends only on
@@ -397,7 +397,8 @@ template <class T>
 GramPlan gram_plan(int64_t n, int p, int q, bool same_operand);
 template <class T>
 void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int p, const T* B,
-                      int64_t ldb, int q, double* C, int64_t ldc, double* part, hipStream_t s);
+                      int64_t ldb, int q, double* C, int64_t ldc, double* part, hipStream_t s,
+                      double scale = 1.0);
 // Device address of the fixed Gram scratch (kGramScratchBytes) on the current
 // device; looked up once per device.
 constexpr size_t kGramScratchBytes = MBL_GRAM_SCRATCH_BYTES;
@@ -406,7 +407,18 @@ double* gram_scratch();
 // Y = A C (+ beta Y), C FP64 (p x q).
 template <class T>
 void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc, T* Y,
-                    int64_t ldy, int q, double beta, hipStream_t s);
+                    int64_t ldy, int q, double beta, hipStream_t s, double scale = 1.0,
+                    const double* colscale = nullptr);
+// Y may be A (ldy = lda): every wavefront reads the rows that it writes, all of them first.
+bool combine_in_place(int64_t n, int q);
+// R = sign A - X diag(mu), mu on the device; A may be R.
+template <class T>
+void launch_residual(int64_t n, int b, const T* A, int64_t lda, double sign, const T* X,
+                     int64_t ldx, const double* mu, T* R, int64_t ldr, hipStream_t s);
+// Ritz coefficients: C = V[:, 0:b] (m x b), Ch = C with its first b rows zero, projected
+// off C twice (m x b, ld b), T1 = Ch^T Ch (b x b).
+void ritz_project(int m, int b, const double* V, double* C, int64_t ldc, double* Ch, double* T1,
+                  hipStream_t s);
 
 // Small dense (single workgroup) FP64 kernels; matrices row-major.
 // small_eigh: ascending eigenvalues w and eigenvectors V (columns) of the

@@ -551,28 +551,29 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int b, const double* __restr
   const int tid = threadIdx.x, nt = blockDim.x;
   double* R = in_lds ? shm : Rg;
   double* Ri = in_lds ? shm + b * b : Rinv;
+  // row j of R holds row j of G until it is formed; rows not kept become zero, and so do,
+  // before the inverse, the entries of R in columns not kept: the sums need no branch
   for (int e = tid; e < b * b; e += nt) {
-    R[e] = 0.0;
+    R[e] = e % b >= e / b ? G[(int64_t)(e / b) * ldg + e % b] : 0.0;
     Ri[e] = 0.0;
   }
   __syncthreads();
   for (int j = 0; j < b; ++j) {
     for (int l = j + tid; l < b; l += nt) {
-      double g = G[(int64_t)j * ldg + l];
-      for (int k = 0; k < j; ++k)
-        if (keep[k]) g -= R[k * b + j] * R[k * b + l];
+      double g = R[j * b + l];
+#pragma unroll 8
+      for (int k = 0; k < j; ++k) g -= R[k * b + j] * R[k * b + l];
       row[l] = g;
     }
     __syncthreads();
     if (tid == 0) {
-      const double gjj = G[(int64_t)j * ldg + j];
+      const double gjj = R[j * b + j];
       const double d = row[j];
       keep[j] = (gjj > 0.0) && (d > tol * gjj) && isfinite(d);
       rjj = keep[j] ? sqrt(d) : 0.0;
     }
     __syncthreads();
-    if (keep[j])
-      for (int l = j + tid; l < b; l += nt) R[j * b + l] = row[l] / rjj;
+    for (int l = j + tid; l < b; l += nt) R[j * b + l] = keep[j] ? row[l] / rjj : 0.0;
     __syncthreads();
   }
   if (tid == 0) {
@@ -583,6 +584,8 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int b, const double* __restr
     }
     *count = c;
   }
+  for (int e = tid; e < b * b; e += nt)
+    if (!keep[e % b]) R[e] = 0.0;
   __syncthreads();
   // row i of R^-1 (kept columns only) from the rows below it
   for (int i = b - 1; i >= 0; --i) {
@@ -596,8 +599,8 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int b, const double* __restr
           continue;
         }
         double s = 0.0;
-        for (int k = i + 1; k <= j; ++k)
-          if (keep[k]) s += R[i * b + k] * Ri[k * b + jc];
+#pragma unroll 8
+        for (int k = i + 1; k <= j; ++k) s += R[i * b + k] * Ri[k * b + jc];
         Ri[i * b + jc] = -s / rii;
       }
     }
@@ -605,6 +608,50 @@ __global__ __launch_bounds__(1024) void k_chol_drop(int b, const double* __restr
   }
   if (in_lds)
     for (int e = tid; e < b * b; e += nt) Rinv[e] = Ri[e];
+}
+
+// ritz_project by one workgroup, with C, Ch and T1 in LDS.
+__global__ __launch_bounds__(1024) void k_ritz_project(int m, int b, const double* __restrict__ V,
+                                                       double* __restrict__ C, int64_t ldc,
+                                                       double* __restrict__ Chg,
+                                                       double* __restrict__ T1g) {
+  extern __shared__ double shm[];
+  double* Cs = shm;          // [m][b]
+  double* Ch = Cs + m * b;   // [m][b]
+  double* T1 = Ch + m * b;   // [b][b]
+  const int tid = threadIdx.x, nt = blockDim.x;
+  for (int e = tid; e < m * b; e += nt) {
+    const int i = e / b, j = e - i * b;
+    const double v = V[(int64_t)i * m + j];
+    Cs[e] = v;
+    Ch[e] = i < b ? 0.0 : v;
+    C[(int64_t)i * ldc + j] = v;
+  }
+  __syncthreads();
+  auto gram = [&](const double* A) {  // T1 = A^T Ch
+    for (int e = tid; e < b * b; e += nt) {
+      const int i = e / b, j = e - i * b;
+      double s = 0.0;
+#pragma unroll 4
+      for (int k = 0; k < m; ++k) s += A[k * b + i] * Ch[k * b + j];
+      T1[e] = s;
+    }
+    __syncthreads();
+  };
+  for (int pass = 0; pass < 2; ++pass) {
+    gram(Cs);
+    for (int e = tid; e < m * b; e += nt) {  // Ch -= C T1
+      const int i = e / b, j = e - i * b;
+      double s = 0.0;
+#pragma unroll 4
+      for (int k = 0; k < b; ++k) s += Cs[i * b + k] * T1[k * b + j];
+      Ch[e] -= s;
+    }
+    __syncthreads();
+  }
+  gram(Ch);
+  for (int e = tid; e < m * b; e += nt) Chg[e] = Ch[e];
+  for (int e = tid; e < b * b; e += nt) T1g[e] = T1[e];
 }
 
 // C = alpha op(A) op(B) + beta C for small row-major FP64 matrices.
@@ -765,7 +812,10 @@ int chol_drop(int b, const double* G, int64_t ldg, double tol, double* Rinv, dou
   if (in_lds)
     MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_chol_drop),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm));
-  hipLaunchKernelGGL(k_chol_drop, dim3(1), dim3(1024), shm, s, b, G, ldg, tol, in_lds, work, Rinv,
+  // A column per thread, so few wavefronts at the many barriers; with G read ahead of the
+  // row loop 18 us (b = 4 and 32 mixed, as in a solve of block 32), before 30.
+  const int nt = in_lds ? (b + 63) / 64 * 64 : 1024;
+  hipLaunchKernelGGL(k_chol_drop, dim3(1), dim3(nt), shm, s, b, G, ldg, tol, in_lds, work, Rinv,
                      dcount);
   MBL_CHECK_LAUNCH();
   int c = 0;
@@ -784,6 +834,30 @@ void small_gemm(int M, int N, int K, double alpha, const double* A, int64_t lda,
   MBL_CHECK_LAUNCH();
 }
 
+// In LDS up to 64 KB (b = 34 at m = 3b; m = 96, b = 32: one launch of 20 us, m = 12, b = 4 one
+// of 5, for three copies and five products of 4 each and the gaps between them), else by the
+// general products.
+void ritz_project(int m, int b, const double* V, double* C, int64_t ldc, double* Ch, double* T1,
+                  hipStream_t s) {
+  const size_t lds = ((size_t)2 * m * b + (size_t)b * b) * sizeof(double);
+  if (lds <= 64 * 1024) {
+    PhaseTick tick(PhaseClock::SMALL, s);
+    const int nt = std::min(1024, (m * b + 63) / 64 * 64);
+    hipLaunchKernelGGL(k_ritz_project, dim3(1), dim3(nt), lds, s, m, b, V, C, ldc, Ch, T1);
+    MBL_CHECK_LAUNCH();
+    return;
+  }
+  MBL_HIP(hipMemcpy2DAsync(C, ldc * sizeof(double), V, m * sizeof(double), b * sizeof(double), m,
+                           hipMemcpyDeviceToDevice, s));
+  MBL_HIP(hipMemcpy2DAsync(Ch, b * sizeof(double), V, m * sizeof(double), b * sizeof(double), m,
+                           hipMemcpyDeviceToDevice, s));
+  MBL_HIP(hipMemsetAsync(Ch, 0, (size_t)b * b * sizeof(double), s));
+  for (int pass = 0; pass < 2; ++pass) {
+    small_gemm(b, b, m, 1.0, C, ldc, true, Ch, b, false, 0.0, T1, b, s);
+    small_gemm(m, b, b, -1.0, C, ldc, false, T1, b, false, 1.0, Ch, b, s);
+  }
+  small_gemm(b, b, m, 1.0, Ch, b, true, Ch, b, false, 0.0, T1, b, s);
+}
 
 void gather_cols(int rows, int nsel, const int* sel, const double* Z, int64_t ldz, double* out,
                  int64_t ldo, hipStream_t s) {

@@ -220,6 +220,11 @@ class Phase {
       const int k = chol_drop(q, sm_.T1.as<double>(), q, drop_tol<TB>(), sm_.Rinv.as<double>(),
                               sm_.cw.as<double>(), sm_.cnt.as<int>(), s_);
       // Rinv is q x q with ld q, first k columns meaningful
+      if (combine_in_place(H_.n, k)) {
+        launch_combine<TB>(H_.n, X, ldx, q, sm_.Rinv.as<double>(), q, X, ldx, k, 0.0, s_);
+        q = k;
+        continue;
+      }
       launch_combine<TB>(H_.n, X, ldx, q, sm_.Rinv.as<double>(), q, B_.tmp.template as<TB>(), p_.b,
                          k, 0.0, s_);
       copy_cols<TB>(H_.n, k, B_.tmp.template as<TB>(), p_.b, X, ldx, s_);
@@ -257,44 +262,33 @@ class Phase {
     TB* HS2 = B_.HS[1 - cur_].template as<TB>();
     double* M = sm_.M.as<double>();
     if (p_.fold)
-      launch_gram<TB>(n, HS, B_.ld, mact, HS, B_.ld, mact, M, mact, s_);
+      launch_gram<TB>(n, HS, B_.ld, mact, HS, B_.ld, mact, M, mact, s_, p_.sign);
     else
-      launch_gram<TB>(n, S, B_.ld, mact, HS, B_.ld, mact, M, mact, s_);
-    if (p_.sign != 1.0)
-      small_gemm(mact, mact, 0, 0.0, M, mact, false, M, mact, false, p_.sign, M, mact, s_);
+      launch_gram<TB>(n, S, B_.ld, mact, HS, B_.ld, mact, M, mact, s_, p_.sign);
     small_eigh(mact, M, mact, sm_.w.as<double>(), sm_.V.as<double>(), mact, sm_.ew.as<double>(),
                s_);
     mu_.resize(b);
     MBL_HIP(hipMemcpyAsync(mu_.data(), sm_.w.as<double>(), b * sizeof(double),
                            hipMemcpyDeviceToHost, s_));
-    // C = V[:, 0:b] (mact x b, ld b)
-    double* C = sm_.C.as<double>();
-    MBL_HIP(hipMemcpy2DAsync(C, b * sizeof(double), sm_.V.as<double>(), mact * sizeof(double),
-                             b * sizeof(double), mact, hipMemcpyDeviceToDevice, s_));
-    // X' = S C, HX' = HS C
-    launch_combine<TB>(n, S, B_.ld, mact, C, b, S2, B_.ld, b, 0.0, s_);
-    launch_combine<TB>(n, HS, B_.ld, mact, C, b, HS2, B_.ld, b, 0.0, s_);
+    // C = V[:, 0:b]; with P and W also C^ = C with the X rows zeroed, projected off C
+    // twice, orthonormalised: [X' P'] = S [C C^], and the same of HS
+    double* C = sm_.C.as<double>();  // mact x 2b
+    const int ldc = 2 * b;
     int bp_new = 0;
     if (mact > b) {
-      // C^ = C with the X rows zeroed, projected off C twice, orthonormalised.
       double* Ch = sm_.Ch.as<double>();
-      MBL_HIP(hipMemcpyAsync(Ch, C, (size_t)mact * b * sizeof(double), hipMemcpyDeviceToDevice,
-                             s_));
-      MBL_HIP(hipMemsetAsync(Ch, 0, (size_t)b * b * sizeof(double), s_));
       double* T1 = sm_.T1.as<double>();
-      for (int pass = 0; pass < 2; ++pass) {
-        small_gemm(b, b, mact, 1.0, C, b, true, Ch, b, false, 0.0, T1, b, s_);   // C^T C^
-        small_gemm(mact, b, b, -1.0, C, b, false, T1, b, false, 1.0, Ch, b, s_);  // C^ -= C T1
-      }
-      small_gemm(b, b, mact, 1.0, Ch, b, true, Ch, b, false, 0.0, T1, b, s_);
-      const int k = chol_drop(b, T1, b, 1e-14, sm_.Rinv.as<double>(), sm_.cw.as<double>(),
-                              sm_.cnt.as<int>(), s_);
-      double* T2 = sm_.T2.as<double>();
-      small_gemm(mact, k, b, 1.0, Ch, b, false, sm_.Rinv.as<double>(), b, false, 0.0, T2, b, s_);
-      launch_combine<TB>(n, S, B_.ld, mact, T2, b, S2 + b, B_.ld, k, 0.0, s_);
-      launch_combine<TB>(n, HS, B_.ld, mact, T2, b, HS2 + b, B_.ld, k, 0.0, s_);
-      bp_new = k;
+      ritz_project(mact, b, sm_.V.as<double>(), C, ldc, Ch, T1, s_);
+      bp_new = chol_drop(b, T1, b, 1e-14, sm_.Rinv.as<double>(), sm_.cw.as<double>(),
+                         sm_.cnt.as<int>(), s_);
+      small_gemm(mact, bp_new, b, 1.0, Ch, b, false, sm_.Rinv.as<double>(), b, false, 0.0, C + b,
+                 ldc, s_);
+    } else {
+      MBL_HIP(hipMemcpy2DAsync(C, ldc * sizeof(double), sm_.V.as<double>(), mact * sizeof(double),
+                               b * sizeof(double), mact, hipMemcpyDeviceToDevice, s_));
     }
+    launch_combine<TB>(n, S, B_.ld, mact, C, ldc, S2, B_.ld, b + bp_new, 0.0, s_);
+    launch_combine<TB>(n, HS, B_.ld, mact, C, ldc, HS2, B_.ld, b + bp_new, 0.0, s_);
     cur_ = 1 - cur_;
     bp_ = bp_new;
     MBL_HIP(hipStreamSynchronize(s_));
@@ -310,40 +304,22 @@ class Phase {
     TB* X = B_.S[cur_].template as<TB>();
     TB* HX = B_.HS[cur_].template as<TB>();
     double* K = sm_.K.as<double>();
-    launch_gram<TB>(n, X, B_.ld, b, HX, B_.ld, b, K, b, s_);
-    if (p_.sign != 1.0) small_gemm(b, b, 0, 0.0, K, b, false, K, b, false, p_.sign, K, b, s_);
+    launch_gram<TB>(n, X, B_.ld, b, HX, B_.ld, b, K, b, s_, p_.sign);
     small_eigh(b, K, b, sm_.th.as<double>(), sm_.Z.as<double>(), b, sm_.ew.as<double>(), s_);
     std::vector<double> th_all(b);
     MBL_HIP(hipMemcpyAsync(th_all.data(), sm_.th.as<double>(), b * sizeof(double),
                            hipMemcpyDeviceToHost, s_));
-    MBL_HIP(hipStreamSynchronize(s_));
-    last_theta_all_ = th_all;
     // residuals of all b H-Ritz pairs: R = sign*HX Z - X Z diag(theta)
-    double* Zt = sm_.T1.as<double>();
-    MBL_HIP(hipMemcpyAsync(Zt, sm_.Z.as<double>(), (size_t)b * b * sizeof(double),
-                           hipMemcpyDeviceToDevice, s_));
-    h_Dc_.assign((size_t)b * b, 0.0);
-    for (int j = 0; j < b; ++j) h_Dc_[(size_t)j * b + j] = -th_all[j];
-    MBL_HIP(hipMemcpyAsync(sm_.T2.get(), h_Dc_.data(), h_Dc_.size() * sizeof(double),
-                           hipMemcpyHostToDevice, s_));
-    small_gemm(b, b, b, 1.0, sm_.Z.as<double>(), b, false, sm_.T2.as<double>(), b, false, 0.0, Zt, b,
-               s_);
     TB* Rr = B_.tmp.template as<TB>();
-    if (p_.sign != 1.0) {
-      double* Zsg = sm_.Ch.as<double>();
-      MBL_HIP(hipMemcpyAsync(Zsg, sm_.Z.as<double>(), (size_t)b * b * sizeof(double),
-                             hipMemcpyDeviceToDevice, s_));
-      small_gemm(b, b, 0, 0.0, Zsg, b, false, Zsg, b, false, p_.sign, Zsg, b, s_);
-      launch_combine<TB>(n, HX, B_.ld, b, Zsg, b, Rr, b, b, 0.0, s_);
-    } else {
-      launch_combine<TB>(n, HX, B_.ld, b, sm_.Z.as<double>(), b, Rr, b, b, 0.0, s_);
-    }
-    launch_combine<TB>(n, X, B_.ld, b, Zt, b, Rr, b, b, 1.0, s_);
+    launch_combine<TB>(n, HX, B_.ld, b, sm_.Z.as<double>(), b, Rr, b, b, 0.0, s_, p_.sign);
+    launch_combine<TB>(n, X, B_.ld, b, sm_.Z.as<double>(), b, Rr, b, b, 1.0, s_, -1.0,
+                       sm_.th.as<double>());
     launch_gram<TB>(n, Rr, b, b, Rr, b, b, sm_.K.as<double>(), b, s_);
     std::vector<double> G((size_t)b * b);
     MBL_HIP(hipMemcpyAsync(G.data(), sm_.K.as<double>(), G.size() * sizeof(double),
                            hipMemcpyDeviceToHost, s_));
     MBL_HIP(hipStreamSynchronize(s_));
+    last_theta_all_ = th_all;
     std::vector<double> r_all(b);
     for (int j = 0; j < b; ++j) r_all[j] = std::sqrt(std::max(0.0, G[(size_t)j * b + j]));
     // The wanted pairs.  Fold: the nev H-Ritz pairs whose vectors x have the
@@ -446,21 +422,12 @@ class Phase {
     const int keep = (int)act.size();
     const auto t_res = clk::now();
     // A-residual R = sign*(op) applied to HX minus X diag(mu)
-    h_D_.assign((size_t)b * b, 0.0);
-    for (int j = 0; j < b; ++j) h_D_[(size_t)j * b + j] = -mu_[j];
-    MBL_HIP(hipMemcpyAsync(sm_.T2.get(), h_D_.data(), h_D_.size() * sizeof(double),
-                           hipMemcpyHostToDevice, s_));
     if (p_.fold) {
       apply(HS, B_.ld, R, b, b);
+      launch_residual<TB>(n, b, R, b, 1.0, S, B_.ld, sm_.w.as<double>(), R, b, s_);
     } else {
-      // R = sign * HX
-      h_I_.assign((size_t)b * b, 0.0);
-      for (int j = 0; j < b; ++j) h_I_[(size_t)j * b + j] = p_.sign;
-      MBL_HIP(hipMemcpyAsync(sm_.T1.get(), h_I_.data(), h_I_.size() * sizeof(double),
-                             hipMemcpyHostToDevice, s_));
-      launch_combine<TB>(n, HS, B_.ld, b, sm_.T1.as<double>(), b, R, b, b, 0.0, s_);
+      launch_residual<TB>(n, b, HS, B_.ld, p_.sign, S, B_.ld, sm_.w.as<double>(), R, b, s_);
     }
-    launch_combine<TB>(n, S, B_.ld, b, sm_.T2.as<double>(), b, R, b, b, 1.0, s_);
     if (p_.fold && m > 0 && keep < b) {
       TB* Rt = B_.tmp.template as<TB>();
       MBL_HIP(hipMemcpyAsync(sm_.asel.get(), act.data(), keep * sizeof(int),
@@ -472,7 +439,7 @@ class Phase {
       ldRin = keep;
       wq = keep;
     }
-    MBL_HIP(hipStreamSynchronize(s_));
+    if (p_.fold) MBL_HIP(hipStreamSynchronize(s_));
     st_.t_rr += secs(t_res);
     if (p_.fold && m > 0) {
       const auto t0 = clk::now();
@@ -525,9 +492,7 @@ class Phase {
     const int xp = b + bp_;
     for (int pass = 0; pass < 2; ++pass) {
       launch_gram<TB>(n, S, ld, xp, W, ld, wq, sm_.T1.as<double>(), wq, s_);
-      small_gemm(xp, wq, 0, 0.0, sm_.T1.as<double>(), wq, false, sm_.T1.as<double>(), wq, false,
-                 -1.0, sm_.T1.as<double>(), wq, s_);  // negate
-      launch_combine<TB>(n, S, ld, xp, sm_.T1.as<double>(), wq, W, ld, wq, 1.0, s_);
+      launch_combine<TB>(n, S, ld, xp, sm_.T1.as<double>(), wq, W, ld, wq, 1.0, s_, -1.0);
     }
     const int bw = cholqr2(W, ld, wq);
     st_.t_rr += secs(t0);
@@ -574,7 +539,6 @@ class Phase {
   // host sources of small uploads: members, so that each outlives its
   // asynchronous copy (every upload is followed by a stream synchronisation
   // before the member is written again)
-  std::vector<double> h_D_, h_I_, h_Dc_;
   std::vector<int> h_act_, h_sel_;
 };
 

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import basis, observables
+from oracle import basis, hamiltonian, linalg, observables, spectrum
 from paper_2012_00217_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -140,3 +140,23 @@ def test_block_combine_keeps_non_finite_rows_apart():
     good = [r for r in range(40) if r not in (7, 39)]
     assert torch.equal(Y[good], torch.full((38, 3), 5.0, dtype=torch.float64))
     assert torch.isnan(Y[39]).all() and torch.isinf(Y[7]).all()
+
+
+# Bases orthonormalised in place to 32 columns; Ritz coefficients in one workgroup's LDS
+# to a block of 34; single and mixed blocks
+@pytest.mark.parametrize("precision", ["f64", "mixed"])
+@pytest.mark.parametrize("b", [5, 31, 32, 33, 34, 35, 48])
+def test_solve_at_the_block_widths_where_kernels_change(b, precision):
+    L, nev = 10, 4
+    h = workloads.disorder(L, 5.0, 3)
+    _, Ho = hamiltonian.sector_matrix(L, L // 2, 1.0, 1.0, h)
+    emin, emax = spectrum.bounds(Ho)
+    sigma = spectrum.shift_from_density(emin, emax, 0.45)
+    w_ref, _ = spectrum.nearest(Ho, sigma, nev)
+    H = api.Hamiltonian(L, h)
+    ev, V, rs, info = H.solve(sigma, nev, b, tol=1e-10, precision=precision)
+    assert info["status"] == "MBL_OK"
+    assert np.all(np.abs(ev - w_ref) <= 1e-10)
+    assert np.all(linalg.residual_norms(Ho, ev, V.cpu().numpy()) <= 1e-10)
+    lo, hi = H.spectrum_bounds(1e-9)[:2]
+    assert abs(lo - emin) <= 1e-8 and abs(hi - emax) <= 1e-8
