@@ -112,10 +112,12 @@ mbl_status mbl_diagonal(mbl_ham H, double sigma, double* diag_dev,
 
 /* Y = (H - sigma I) X for an n x b block, never forming H.  prec MBL_F64 or
  * MBL_F32 selects the element type of X and Y.  ldx, ldy >= b.  X and Y must
- * not overlap.  Async.  The launch schedule comes from the library's table of
- * tuned schedules (nearest sector size, same row width); the environment
- * variables MBL_APPLY_CHUNK_BYTES, MBL_APPLY_LANE_BYTES, MBL_APPLY_XCD_GROUP and
- * MBL_APPLY_SLOTS_PER_XCD override its fields (they also apply to mbl_pcg).
+ * not overlap.  Async.  Sectors near half filling go by tiles of rows, the others
+ * by the row-major gather kernel (same bits).  The gather kernel's launch schedule
+ * comes from the library's table of tuned schedules (nearest sector size, same row
+ * width); the environment variables MBL_APPLY_CHUNK_BYTES, MBL_APPLY_LANE_BYTES,
+ * MBL_APPLY_XCD_GROUP and MBL_APPLY_SLOTS_PER_XCD override its fields and select that
+ * kernel (they also apply to mbl_pcg).
  * MBL_APPLY_SPLIT=1 selects the two-pass kernel instead (the chain cut in two
  * halves, each half's flips gathered from an LDS tile; also used by mbl_pcg
  * and the solvers); MBL_SPLIT_PANEL_BYTES and MBL_SPLIT_SLOTS override its
@@ -133,9 +135,10 @@ mbl_status mbl_fold_apply(mbl_ham H, double sigma, mbl_precision prec,
 
 /* W = m steps of Jacobi-preconditioned CG on (H - sigma I)^2 W = R, each
  * column independently, starting from W = 0 (the LOBPCG preconditioner,
- * Sec. 3.2).  The kernels are chosen by the sector's size; a launch schedule in
- * the environment (see mbl_apply_block) selects the row-major gather kernels.  prec MBL_F64 or MBL_F32 is the element type of R, W and of the
- * CG arithmetic.  m >= 0.  Synchronises `stream`. */
+ * Sec. 3.2).  The kernels are chosen by the sector's size and filling; a launch
+ * schedule in the environment (see mbl_apply_block) selects the row-major gather
+ * kernels.  prec MBL_F64 or MBL_F32 is the element type of R, W and of the CG
+ * arithmetic.  m >= 0.  Synchronises `stream`. */
 mbl_status mbl_pcg(mbl_ham H, double sigma, mbl_precision prec, const void* R,
                    int64_t ldr, void* W, int64_t ldw, int b, int m,
                    hipStream_t stream);

@@ -1,5 +1,8 @@
 // Matrix-free block apply Y = (H - sigma I) X (paper Sec. 3.2 and 4.1) and the
-// Jacobi-preconditioned CG on the spectral fold (H - sigma I)^2 built from it.
+// Jacobi-preconditioned CG on the spectral fold (H - sigma I)^2 built from it: the choice
+// between the paths (apply_tile.hip, cg_column.hip, cg_panel.hip) and the gather kernels,
+// which serve sectors far from half filling, launch schedules asked for and CG by column
+// chunks.
 //
 // Gather form (H is symmetric, so no atomics):
 //   Y[r,:] = (E(s_r) - sigma) X[r,:] + (J/2) sum_{bonds i active in s_r} X[r +- C(i,t), :]
@@ -748,16 +751,16 @@ ApplyArgs<T> base_args(const Ham& H, double sigma) {
   return a;
 }
 
-}  // namespace
-
 // A launch schedule or the two-pass kernels asked for through the environment
-// concern the gather kernels: the CG then runs on those.
+// concern the gather kernels: applies and CG then run on those.
 bool gather_forced() {
   for (const char* v : {"MBL_APPLY_CHUNK_BYTES", "MBL_APPLY_LANE_BYTES", "MBL_APPLY_XCD_GROUP",
                         "MBL_APPLY_SLOTS_PER_XCD"})
     if (std::getenv(v)) return true;
   return env_int("MBL_APPLY_SPLIT", 0) != 0;
 }
+
+}  // namespace
 
 template <class T>
 void launch_apply(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int64_t ldy, int w,

@@ -502,10 +502,10 @@ __device__ inline double half_energy(const PanelTabArgs& a, int base, int len, u
 
 // First row of the block of hi: the rank of its up spins, which come after the
 // kl up spins of the low half.
-__device__ inline int block_row(const PanelTabArgs& a, uint32_t hi, int kl) {
+__device__ inline int block_row(const PanelTabArgs& a, const uint32_t* C, uint32_t hi, int kl) {
   int row = 0, j = 0;
   for (int p = 0; p < a.Lh; ++p)
-    if ((hi >> p) & 1u) row += (int)a.pascal[(a.q + p) * kPascal + kl + ++j];
+    if ((hi >> p) & 1u) row += (int)C[(a.q + p) * kPascal + kl + ++j];
   return row;
 }
 
@@ -541,13 +541,13 @@ __device__ const Subsets kSubsets = Subsets();
 // The two values of the lowest site follow each other, so a group of tiles is a number of
 // equal pairs (where both have rows) and the first tile of a row count is a division
 // (first_tile).
-__device__ inline int tile_rank(const PanelTabArgs& a, uint32_t hi) {
-  auto rows = [&](int kl) { return kl < 0 || kl > a.q ? 0 : (int)a.pascal[a.q * kPascal + kl]; };
+__device__ inline int tile_rank(const PanelTabArgs& a, const uint32_t* C, uint32_t hi) {
+  auto rows = [&](int kl) { return kl < 0 || kl > a.q ? 0 : (int)C[a.q * kPascal + kl]; };
   const int m = a.Lh - 1;
   int c = __popc(hi >> 1), sum = 0, t = 0;
   for (uint32_t w = hi >> 1; w; w &= w - 1) sum += __ffs(w) - 1;
   for (int g = 0; g < c; ++g)
-    t += (int)a.pascal[m * kPascal + g] * ((rows(a.k - g) > 0) + (rows(a.k - g - 1) > 0));
+    t += (int)C[m * kPascal + g] * ((rows(a.k - g) > 0) + (rows(a.k - g - 1) > 0));
   const int even = rows(a.k - c) > 0, odd = rows(a.k - c - 1) > 0;
   int i = kSubsets.below[m][c][sum];
   for (int b = m - 1; b >= 0; --b)
@@ -561,9 +561,13 @@ __device__ inline int tile_rank(const PanelTabArgs& a, uint32_t hi) {
 
 // One thread per low configuration and one per high configuration; a tile is one of those
 // that have rows in the sector.
-__global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
+// blockIdx.y: the tables of the panels or of the apply.
+__global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a0, PanelTabArgs a1) {
+  __shared__ uint32_t C[kPascal * kPascal];  // read in serial chains
+  const PanelTabArgs& a = blockIdx.y == 0 ? a0 : a1;
+  for (int i = threadIdx.x; i < kPascal * kPascal; i += 256) C[i] = a.pascal[i];
+  __syncthreads();
   const uint32_t id = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t* C = a.pascal;
   auto binom = [&](int i, int t) { return t < 0 || t > i ? 0 : (int)C[i * kPascal + t]; };
   if (id < (1u << a.q)) {
     // by (up spins, value); the flips as rows of the LDS tile (row u at u + 1,
@@ -596,25 +600,25 @@ __global__ __launch_bounds__(256) void k_panel_tables(PanelTabArgs a) {
     const int kl = a.k - __popc(v);
     if (kl < 0 || kl > a.q) return;
     PanelTile t{};
-    t.row0 = block_row(a, v, kl);
+    t.row0 = block_row(a, C, v, kl);
     t.nrows = binom(a.q, kl);
     for (int c = 0; c < kl; ++c) t.aux += binom(a.q, c);
     t.E = half_energy(a, a.q, a.Lh, v, &t.nd);
     for (int b = 0; b + 1 < a.Lh; ++b)
       if (((v >> b) ^ (v >> (b + 1))) & 1u)
-        t.off[t.cnt++] = block_row(a, v ^ (3u << b), kl) - t.row0;
+        t.off[t.cnt++] = block_row(a, C, v ^ (3u << b), kl) - t.row0;
     // middle bond: even hi, the rows with the top low site up (the last
     // C(11, kl - 1)) land on the first rows of hi | 1; odd hi, the rows with that
     // site down land on the last rows of hi & ~1
     const uint32_t pv = v ^ 1u;
     const int pkl = a.k - __popc(pv), split = binom(a.q - 1, kl);
     if (pkl >= 0 && pkl <= a.q) {
-      const int prow = block_row(a, pv, pkl);
+      const int prow = block_row(a, C, pv, pkl);
       t.mlo = (v & 1u) ? 0 : split;
       t.mhi = (v & 1u) ? split : t.nrows;
       t.mbase = (v & 1u) ? prow + binom(a.q - 1, kl + 1) : prow - split;
     }
-    a.tiles[tile_rank(a, v)] = t;
+    a.tiles[tile_rank(a, C, v)] = t;
   }
 }
 
@@ -645,12 +649,13 @@ int first_tile(const Ham& H, const PanelTables& P, int64_t row) {
   return (int)t;
 }
 
-// The tables of P for blocks of q low sites; none where the mean block is short.
-void build_tables_of(Ham& H, PanelTables& P, int q, int mean_rows, hipStream_t s) {
+// The arguments for the tables of P, for blocks of q low sites; false where the mean block
+// is short.
+bool plan_tables(Ham& H, PanelTables& P, int q, int mean_rows, PanelTabArgs* out, hipStream_t s) {
   const int Lh = H.L - q;
   int64_t tiles = 0;
   tile_groups(H, q, [&](int per, int64_t, int64_t, int64_t pairs) { tiles += per * pairs; });
-  if (H.n < mean_rows * tiles) return;
+  if (H.n < mean_rows * tiles) return false;
   P.q = q;
   P.ntiles = (int)tiles;
   const size_t nt = P.ntiles * sizeof(PanelTile), nl = (size_t)1 << q;
@@ -658,7 +663,7 @@ void build_tables_of(Ham& H, PanelTables& P, int q, int mean_rows, hipStream_t s
   P.lo_tab = P.buf.as<uint4>();
   P.lo_E = reinterpret_cast<double*>(P.lo_tab + nl);
   P.tiles = reinterpret_cast<PanelTile*>(P.lo_E + nl);
-  PanelTabArgs a{};
+  PanelTabArgs& a = *out;
   a.L = H.L;
   a.k = H.nup;
   a.q = q;
@@ -669,15 +674,13 @@ void build_tables_of(Ham& H, PanelTables& P, int q, int mean_rows, hipStream_t s
   a.tiles = P.tiles;
   a.lo_tab = P.lo_tab;
   a.lo_E = P.lo_E;
-  const size_t threads = std::max<size_t>(nl, (size_t)1 << Lh);
-  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, a);
-  MBL_CHECK_LAUNCH();
-  P.ok = true;
+  return true;
 }
 
 }  // namespace
 
 void build_panel_tables(Ham& H, hipStream_t s) {
+  PanelTabArgs a[2]{};
   auto fits = [&](int q, int most_high, int64_t least) {
     return H.L - q >= 2 && H.L - q <= most_high && H.n > least;
   };
@@ -693,8 +696,18 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   // 8 up; 64 columns) 69 for 82, 123 (L = 24, 10 up) 555 for 604.  Half filling has 150 to
   // 230.
   if (!H.col_ok && fits(kPanelQ, kPanelMaxHigh, kPanelMinRows) && H.n < (1ll << 28))
-    build_tables_of(H, H.panel, kPanelQ, kPanelMeanRows, s);
-  if (fits(kTileQ, kMaxHigh, kTileMinRows)) build_tables_of(H, H.tile, kTileQ, kTileMeanRows, s);
+    H.panel.ok = plan_tables(H, H.panel, kPanelQ, kPanelMeanRows, &a[0], s);
+  int n = H.panel.ok ? 1 : 0;
+  if (fits(kTileQ, kMaxHigh, kTileMinRows))
+    H.tile.ok = plan_tables(H, H.tile, kTileQ, kTileMeanRows, &a[n], s);
+  if (H.tile.ok) ++n;
+  if (n == 0) return;
+  size_t threads = 0;
+  for (int i = 0; i < n; ++i)
+    threads = std::max({threads, (size_t)1 << a[i].q, (size_t)1 << a[i].Lh});
+  hipLaunchKernelGGL(k_panel_tables, dim3((unsigned)((threads + 255) / 256), n), dim3(256), 0, s,
+                     a[0], a[1]);
+  MBL_CHECK_LAUNCH();
 }
 
 bool panel_usable(const Ham& H, int b) {
