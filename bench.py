@@ -39,7 +39,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 APPLY_SRC = [os.path.join(ROOT, "paper_2012_00217_amd", "csrc", f)
-             for f in ("apply.hip", "apply_schedules.inc")]
+             for f in ("apply.hip", "apply_schedules.inc", "cg_panel.hip", "cg_column.hip")]
 COUNTERS = os.path.join(ROOT, "profiles", "cg_apply_{}_counters.md")  # per workload
 
 WORKLOADS = {
@@ -61,7 +61,7 @@ WORKLOADS = {
 
 
 def apply_src_hash():
-    """Hash of the apply kernel source and its compiled-in launch schedules."""
+    """Hash of the CG kernel sources and the compiled-in launch schedules."""
     h = hashlib.sha256()
     for path in APPLY_SRC:
         with open(path, "rb") as f:
@@ -788,6 +788,10 @@ def main():
     #   apply2  q = (H - sigma) T, x += alpha p, r -= alpha q, r.M^-1 r: read
     #           T, p, x, r, write x, r, state, diagonal, Jacobi diagonal
     #                                                -> 6 n w s + (12 + s) n
+    # and of the panel CG (sectors above 13,312 rows near half filling), whose x
+    # update is elsewhere and whose per-row tables are those of the two halves:
+    #   apply1  read p, write T                      -> 2 n w s
+    #   apply2  read T, r, write r                   -> 3 n w s
     # dominant: the larger total time (both kernels run once per CG step)
     dom = max(tot, key=lambda kk: tot[kk][1])
     nl, ms_all, bytes_all, nsample, ms_sample = tot[dom]
@@ -807,7 +811,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBPS, 4),
                 "traffic": traffic,
-                "kernel": f"k_apply fused CG {dom} ({'FP64' if s == 8 else 'FP32'}, "
+                "kernel": f"fused CG {dom} ({'FP64' if s == 8 else 'FP32'}, "
                           + (", ".join(f"{c} launches over {w} columns"
                                        for w, c in widths.items()) if widths else
                              f"{wl['block']}-column block, narrower once pairs lock"
