@@ -493,7 +493,9 @@ double* gram_scratch() {
   return g_scratch[dev];
 }
 
-bool combine_wide(int64_t n, int q) { return q > 32 && n >= 32768; }
+bool combine_wide(int64_t n, int q) {
+  return q > 32 && (n >= 32768 || q > 32 * 65535);  // second: blocks of a grid
+}
 
 template <class T, int NB, int NW>
 void launch_combine_as(int64_t n, const T* A, int64_t lda, int p, const double* C, int64_t ldc,

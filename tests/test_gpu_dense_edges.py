@@ -160,3 +160,19 @@ def test_solve_at_the_block_widths_where_kernels_change(b, precision):
     assert np.all(linalg.residual_norms(Ho, ev, V.cpu().numpy()) <= 1e-10)
     lo, hi = H.spectrum_bounds(1e-9)[:2]
     assert abs(lo - emin) <= 1e-8 and abs(hi - emax) <= 1e-8
+
+
+def test_block_combine_under_graph_capture():
+    """The wide form with more than 64 KB of LDS (C of 192 x 64 in FP64)."""
+    A, Cm = _block(32800, 192, torch.float64, 5), _block(192, 64, torch.float64, 6)
+    ref = api.block_combine(A, Cm)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = api.block_combine(A, Cm)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
