@@ -119,12 +119,12 @@ __device__ inline double wave_cols(const double (&v)[VE]) {
 // larger workgroups in flight (4 of 256, 4 of 512 threads per CU) and blocks of q = 11 or
 // 10 are slower (590 and 553, 600 and 700 us; the second apply 710 and 771, 735 and
 // 852 against 662), eight loads of the high half at once give nothing.
-template <class T, int EPI>
-__global__ __launch_bounds__(kPThreads) void k_panel(PanelArgs<T> a) {
+template <class T, int EPI, int NT>
+__global__ __launch_bounds__(NT) void k_panel(PanelArgs<T> a) {
   using V = typename PV<T>::type;
   constexpr int VE = 16 / (int)sizeof(T);
   __shared__ V tile[kPanelRows + 1];  // row u at tile[u + 1]; tile[0] stays zero
-  __shared__ double sred[kPWaves][VE];
+  __shared__ double sred[NT / 64][VE];
   __shared__ int snext;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kPThreads) void k_panel(PanelArgs<T> a) {
     const MBL_CONST PanelTile* tp = (const MBL_CONST PanelTile*)a.tiles + t;
     const int nr = tp->nrows, row0 = tp->row0, cnt = tp->cnt, aux = tp->aux;
     const int mlo = tp->mlo, mhi = tp->mhi;
-    for (int u = tid; u < nr; u += kPThreads) tile[u + 1] = pload<T>(X, (uint32_t)(row0 + u) * 16u);
+    for (int u = tid; u < nr; u += NT) tile[u + 1] = pload<T>(X, (uint32_t)(row0 + u) * 16u);
     T alpha[VE];
     if constexpr (EPI == PAN_RUPD) {
       const MBL_CONST PcgCoef* cf = (const MBL_CONST PcgCoef*)a.coef + panel * VE;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kPThreads) void k_panel(PanelArgs<T> a) {
     for (int e = 0; e < VE; ++e) red[e] = 0.0;
     const char* tb = reinterpret_cast<const char*>(tile);
     __syncthreads();
-    for (int u0 = wave * 64; u0 < nr; u0 += kPThreads) {
+    for (int u0 = wave * 64; u0 < nr; u0 += NT) {
       // Lanes past the last row repeat it (so that loads are unconditional) and
       // store nothing.
       const int ul = u0 + lane, u = min(ul, nr - 1);
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kPThreads) void k_panel(PanelArgs<T> a) {
     if (tid < VE) {
       double s = sred[0][tid];
 #pragma unroll
-      for (int v = 1; v < kPWaves; ++v) s += sred[v][tid];
+      for (int v = 1; v < NT / 64; ++v) s += sred[v][tid];
       a.part[((int64_t)panel * VE + tid) * a.ts.ntiles + t] = s;
     }
     lt = __builtin_amdgcn_readfirstlane(snext);
@@ -721,6 +721,13 @@ namespace {
 // and 1.88 ms with 3, 4, 6 and 8; at L = 20 (64 FP64 columns) 245, 228, 217, 217 us.
 constexpr int kPanelPerCu = 8;
 
+// Few tiles leave the card short of wavefronts: up to this number 512 threads take one.
+// CG of 16 steps with 256 and 512: 256 tiles (L = 17, 32 FP32 columns) 743 and 673 us, 1024
+// (L = 18, 32 FP64) 1119 and 1070, 2048 (L = 21, 8 FP64) 1691 and 1527, 4096 (L = 20, 32
+// FP64) 2267 and 2184; 8192 (L = 20, 64 FP64) 3674 and 3666, (L = 24, 8 FP32) 5318 and 5370;
+// at L = 24 with 64 columns the second apply takes 662 and 771.
+constexpr int64_t kPanelWideTiles = 4096;
+
 }  // namespace
 
 PanelSched panel_sched(const Ham& H, const PanelTables& P, int npan, int slots) {
@@ -795,6 +802,7 @@ void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t
 
   // CG steps [from, to) on the leading np panels; columns from `cols` on are frozen
   auto steps = [&](int np, int cols, int from, int to) {
+    const bool wide = (int64_t)np * P.ntiles <= kPanelWideTiles;
     const PanelSched ts = panel_sched(H, P, np, 32 * kPanelPerCu);
     PanelArgs<T> a1{};
     a1.tiles = P.tiles;
@@ -817,7 +825,11 @@ void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t
     eu.npan = np;
     eu.b = std::min(b, np * VE);
     auto apply = [&](auto epi, const PanelArgs<T>& a, hipStream_t st) {
-      hipLaunchKernelGGL((k_panel<T, decltype(epi)::value>), dim3(ts.nwg), dim3(kPThreads), 0, st, a);
+      constexpr int E = decltype(epi)::value;
+      if (wide)
+        hipLaunchKernelGGL((k_panel<T, E, 512>), dim3(ts.nwg), dim3(512), 0, st, a);
+      else
+        hipLaunchKernelGGL((k_panel<T, E, 256>), dim3(ts.nwg), dim3(256), 0, st, a);
       MBL_CHECK_LAUNCH();
     };
     using E1 = std::integral_constant<int, PAN_NORM2>;
