@@ -305,11 +305,12 @@ def run_precision(args):
 def run_cgstep(args):
     """Time of one block Jacobi-PCG step and of one plain apply (H - sigma) X,
     per kernel path: `--cases` lists L:block:dtype (W=4, seed 0, Sz=0), and
-    `--modes` the apply kernels (onepass: the one-pass gather kernel, split:
+    `--modes` the apply kernels (onepass: those that the library picks, split:
     the two-pass kernel, MBL_APPLY_SPLIT=1).  The CG step time is the
     difference of two PCG calls of m1 and m2 steps over m2 - m1 (setup and
     the first steps cancel); algorithmic bytes of a CG step: apply1 2nbs,
-    apply2 6nbs, p update 3nbs (11nbs, plus per-row tables)."""
+    apply2 6nbs, p update 3nbs (11nbs, plus per-row tables) with the gather
+    kernels, 2nbs, 3nbs and 5nbs (10nbs) with the panels; reported at 11nbs."""
     import torch
     from paper_2012_00217_amd import api, workloads
 

@@ -1,6 +1,7 @@
-"""Launch-schedule autotuner for the apply and CG kernels (MI355X).
+"""Launch-schedule autotuner for the gather kernels of the apply and CG (MI355X).
 
-The apply kernel and the fused CG kernels take four launch parameters:
+These kernels (sectors far from half filling, and every call with a schedule
+in the environment) take four launch parameters:
 bytes of a row chunk, bytes per lane, tiles per XCD group and workgroups per
 XCD.  Which combination is fastest depends on the sector dimension (how far the
 high-bond gathers reach compared with an XCD's L2 and the last-level cache) and
