@@ -408,9 +408,13 @@ __global__ __launch_bounds__(1024) void k_jacobi_values(const double* __restrict
   jacobi_body<kVecNone, NB>(t.dim, A + t.a_at, t.dim, o, jw);
 }
 
-// V from the recorded rotations: one wavefront applies all of them to its rows of
-// the identity, then stores the columns in the order of the eigenvalues.
-constexpr int kVecRows = 4;
+// V from the recorded rotations: one wavefront applies all of them to its row of the
+// identity, then stores the row in the order of the eigenvalues.  Bound by the latency of
+// the records and the wavefront's issue: m = 192 takes 460 us with one row per wavefront and
+// 8 rounds on their way, 790 with one round, 830 with four rows and one round, 850 with
+// four rows and 8 rounds (m = 96: 181, 330, 278, 276).
+constexpr int kVecRows = 1;
+constexpr int kVecAhead = 8;
 __global__ __launch_bounds__(64) void k_jacobi_vectors(int m, const double2* __restrict__ rec,
                                                        const int* __restrict__ info,
                                                        double* __restrict__ V, int64_t ldv) {
@@ -423,37 +427,46 @@ __global__ __launch_bounds__(64) void k_jacobi_vectors(int m, const double2* __r
   }
   const int rounds = info[0];
   constexpr int kL = (kLdsMax / 2 + 63) / 64;  // pairs per lane
-  double2 next[kL];
-  auto fetch = [&](int rd) {
+  double2 next[kVecAhead][kL];
+  auto fetch = [&](int rd0) {
 #pragma unroll
-    for (int t = 0; t < kL; ++t) {
-      const int l = lane + 64 * t;
-      next[t] = l < np ? rec[(int64_t)rd * np + l] : make_double2(1.0, 0.0);
-    }
+    for (int d = 0; d < kVecAhead; ++d)
+#pragma unroll
+      for (int t = 0; t < kL; ++t) {
+        const int l = lane + 64 * t;
+        next[d][t] = l < np && rd0 + d < rounds ? rec[(int64_t)(rd0 + d) * np + l]
+                                                : make_double2(1.0, 0.0);
+      }
   };
   Pair pair[kL] = {Pair(mm, 0, min(lane, np - 1)), Pair(mm, 0, min(lane + 64, np - 1))};
   static_assert(kL == 2, "pairs per lane");
   if (rounds > 0) fetch(0);
   __syncthreads();
-  for (int rd = 0; rd < rounds; ++rd) {
-    double2 c[kL];
+  for (int rd = 0; rd < rounds; rd += kVecAhead) {
+    double2 cur[kVecAhead][kL];
 #pragma unroll
-    for (int t = 0; t < kL; ++t) c[t] = next[t];
-    if (rd + 1 < rounds) fetch(rd + 1);
+    for (int d = 0; d < kVecAhead; ++d)
 #pragma unroll
-    for (int t = 0; t < kL; ++t) {
-      if (lane + 64 * t < np && c[t].y != 0.0) {
-        const int p = pair[t].a, q = pair[t].b;
+      for (int t = 0; t < kL; ++t) cur[d][t] = next[d][t];
+    fetch(rd + kVecAhead);
 #pragma unroll
-        for (int r = 0; r < kVecRows; ++r) {
-          const double vp = v[r][p], vq = v[r][q];
-          v[r][p] = c[t].x * vp - c[t].y * vq;
-          v[r][q] = c[t].y * vp + c[t].x * vq;
+    for (int d = 0; d < kVecAhead; ++d) {
+#pragma unroll
+      for (int t = 0; t < kL; ++t) {
+        const double2 c = cur[d][t];
+        if (lane + 64 * t < np && c.y != 0.0) {  // rounds beyond the last rotate nothing
+          const int p = pair[t].a, q = pair[t].b;
+#pragma unroll
+          for (int r = 0; r < kVecRows; ++r) {
+            const double vp = v[r][p], vq = v[r][q];
+            v[r][p] = c.x * vp - c.y * vq;
+            v[r][q] = c.y * vp + c.x * vq;
+          }
         }
+        pair[t].step(mm);
       }
-      pair[t].step(mm);
+      __syncthreads();  // one wavefront: orders its LDS accesses
     }
-    __syncthreads();  // one wavefront: orders its LDS accesses
   }
   for (int e = lane; e < kVecRows * m; e += 64) {
     const int r = e / m, j = e - r * m;
