@@ -386,7 +386,7 @@ mbl_status mbl_small_eigh(int m, const double* A_dev, int64_t lda, double* w_dev
     require(A_dev && w_dev && V_dev, "NULL argument");
     require(lda >= m && ldv >= m, "leading dimension < m");
     DevBuf work(small_eigh_work_bytes(m), s);
-    small_eigh(m, A_dev, lda, w_dev, V_dev, ldv, work.as<double>(), s);
+    small_eigh(m, A_dev, lda, w_dev, V_dev, ldv, work, s);
     MBL_HIP(hipStreamSynchronize(s));
     return MBL_OK;
   });

@@ -423,8 +423,9 @@ void ritz_project(int m, int b, const double* V, double* C, int64_t ldc, double*
 // Small dense (single workgroup) FP64 kernels; matrices row-major.
 // small_eigh: ascending eigenvalues w and eigenvectors V (columns) of the
 // symmetric A; V == nullptr asks for eigenvalues only (m <= 192).
+// Refuses a workspace of less than small_eigh_work_bytes(m).
 void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64_t ldv,
-                double* work, hipStream_t s);
+                const DevBuf& workspace, hipStream_t s);
 
 // Eigenvalues of `count` matrices (dim <= max_dim <= 192, row-major, at A + a_at) in one
 // launch, ascending at w + w_at.
@@ -435,7 +436,7 @@ struct EighItem {
 void eigh_values(int count, int max_dim, const double* A, const EighItem* items_dev, double* w,
                  hipStream_t s);
 
-// Workspace bytes needed by small_eigh for size m.
+// Workspace bytes that serve small_eigh for every size up to m.
 size_t small_eigh_work_bytes(int m);
 
 template <class S, class D>

@@ -698,13 +698,15 @@ inline unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
+// Non-decreasing in m: a workspace for the largest size serves every smaller one, though
+// the sizes to kLdsMax need more (every round's rotations, their number and the column
+// order) than some above it (two copies of A and V).
 size_t small_eigh_work_bytes(int m) {
-  const int64_t mm = m + (m & 1);
-  size_t bytes = (size_t)(3 * mm * mm) * sizeof(double) + 256;
-  if (mm <= kLdsMax)  // every round's rotations, their number and the column order
-    bytes = std::max(bytes, (size_t)kMaxSweeps * (mm - 1) * (mm / 2) * sizeof(double2) +
-                                (size_t)(mm + 1) * sizeof(int) + 256);
-  return bytes;
+  const int64_t mm = m + (m & 1), lm = std::min<int64_t>(mm, kLdsMax);
+  return std::max((size_t)(3 * mm * mm) * sizeof(double),
+                  (size_t)kMaxSweeps * (lm - 1) * (lm / 2) * sizeof(double2) +
+                      (size_t)(lm + 1) * sizeof(int)) +
+         256;
 }
 
 namespace {
@@ -746,9 +748,12 @@ void eigh_values(int count, int max_dim, const double* A, const EighItem* items_
 }
 
 void small_eigh(int m, const double* A, int64_t lda, double* w, double* V, int64_t ldv,
-                double* work, hipStream_t s) {
+                const DevBuf& workspace, hipStream_t s) {
   PhaseTick tick(PhaseClock::SMALL, s);
   if (m <= 0) return;
+  if (workspace.bytes() < small_eigh_work_bytes(m))
+    fail(MBL_EINTERNAL, "small_eigh: workspace too small");
+  double* work = workspace.as<double>();
   const int mm = m + (m & 1);
   const int max_sweeps = kMaxSweeps;
   if (m == 1) {

@@ -265,8 +265,7 @@ class Phase {
       launch_gram<TB>(n, HS, B_.ld, mact, HS, B_.ld, mact, M, mact, s_, p_.sign);
     else
       launch_gram<TB>(n, S, B_.ld, mact, HS, B_.ld, mact, M, mact, s_, p_.sign);
-    small_eigh(mact, M, mact, sm_.w.as<double>(), sm_.V.as<double>(), mact, sm_.ew.as<double>(),
-               s_);
+    small_eigh(mact, M, mact, sm_.w.as<double>(), sm_.V.as<double>(), mact, sm_.ew, s_);
     mu_.resize(b);
     MBL_HIP(hipMemcpyAsync(mu_.data(), sm_.w.as<double>(), b * sizeof(double),
                            hipMemcpyDeviceToHost, s_));
@@ -305,7 +304,7 @@ class Phase {
     TB* HX = B_.HS[cur_].template as<TB>();
     double* K = sm_.K.as<double>();
     launch_gram<TB>(n, X, B_.ld, b, HX, B_.ld, b, K, b, s_, p_.sign);
-    small_eigh(b, K, b, sm_.th.as<double>(), sm_.Z.as<double>(), b, sm_.ew.as<double>(), s_);
+    small_eigh(b, K, b, sm_.th.as<double>(), sm_.Z.as<double>(), b, sm_.ew, s_);
     std::vector<double> th_all(b);
     MBL_HIP(hipMemcpyAsync(th_all.data(), sm_.th.as<double>(), b * sizeof(double),
                            hipMemcpyDeviceToHost, s_));

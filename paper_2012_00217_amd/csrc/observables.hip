@@ -233,7 +233,7 @@ void entanglement_entropy(const Ham& H, const double* V, int64_t ldv, int nev, i
       MBL_CHECK_LAUNCH();
       // only the eigenvalues are needed: blocks up to 192 take the values-only path
       double* zv = dim + (dim & 1) <= kBatchDim ? nullptr : Z.as<double>();
-      small_eigh(dim, G.as<double>(), dim, w.as<double>(), zv, dim, work.as<double>(), s);
+      small_eigh(dim, G.as<double>(), dim, w.as<double>(), zv, dim, work, s);
       MBL_HIP(hipMemcpyAsync(p.data(), w.get(), dim * sizeof(double), hipMemcpyDeviceToHost, s));
       MBL_HIP(hipStreamSynchronize(s));
       add_entropy(p.data(), dim, &ent[kA][j]);

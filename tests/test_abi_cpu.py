@@ -93,3 +93,14 @@ def test_gap_ratio_host_routine():
     assert api.gap_ratio(np.arange(12.0)[::-1]) == 1.0
     with pytest.raises(api.MblError):
         api.gap_ratio([1.0, 2.0])
+
+
+def test_eigensolver_workspace_serves_every_smaller_size(lib):
+    """A solve allocates the workspace once, for three blocks of columns, and calls
+    the eigensolver at one, two and three: no size may need more than a larger one."""
+    need = lib._ZN3mbl21small_eigh_work_bytesEi  # mbl::small_eigh_work_bytes(int)
+    need.restype, need.argtypes = C.c_size_t, [C.c_int]
+    sizes = [need(m) for m in range(1, 1025)]
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))
+    # 30 sweeps of 191 rounds of 96 rotations, their count and 192 column places
+    assert sizes[191] >= 30 * 191 * 96 * 16 + 193 * 4
