@@ -81,6 +81,13 @@ def cg_launch_widths(steps, column_steps, block, nev):
     return {block: steps - y, **({nev: y} if y > 0 else {})}
 
 
+def column_cg(n):
+    """The CG of a sector of n rows runs one workgroup per column (every sector of the
+    workloads with at most 13,312 rows, unless the environment asks for a kernel)."""
+    return n <= 13312 and not any(k.startswith(("MBL_APPLY_", "MBL_PCG_CACHE_MB"))
+                                  for k in os.environ)
+
+
 def read_traffic(kernel, workload, precision, width=None):
     """HBM bytes per launch from the committed counter summary, or None if the
     summary is missing, covers another workload or precision, or was taken
@@ -820,6 +827,16 @@ def main():
                 "algorithmic_bytes_per_launch": kb, "avg_launch_us": round(avg_ms * 1e3, 2),
                 "launches": nl, "timed_launches": nsample,
                 "timed_avg_launch_us": round(ms_sample / max(1, nsample) * 1e3, 2)}
+
+    if column_cg(n):
+        # the CG vectors never leave the CU: a memory rate would mean nothing
+        roofline = {"bound": "latency", "achieved": None, "peak": None, "unit": None,
+                    "frac": None, "traffic": None,
+                    "kernel": f"one workgroup per CG column, every step in one launch "
+                              f"({'FP64' if s == 8 else 'FP32'}, {wl['block']} columns)",
+                    "cg_steps": nl,
+                    **{f"{kk}_us_per_step": round(t[1] / max(1, t[0]) * 1e3, 2)
+                       for kk, t in tot.items()}}
 
     # H X bandwidth of the plain apply (after the timed region)
     H0 = hams[wl["Ws"][0]]

@@ -197,8 +197,10 @@ typedef struct {
   int timing;            /* 1: time the two fused CG apply kernels with HIP
                             events on the solve's stream (the first 64 CG
                             steps of every inner CG call and column chunk,
-                            extrapolated to all its steps), and the apply,
-                            Gram and small dense phases                      */
+                            extrapolated to all its steps; by the device
+                            clock where one workgroup runs a column, see
+                            mbl_solve_info), and the apply, Gram and small
+                            dense phases                                     */
   uint64_t seed;         /* starting block (device counter-based generator)  */
   int lock;              /* 1: soft locking.  Wanted pairs whose tracked
                             residual is <= tol/10 keep their place in X and
@@ -254,8 +256,16 @@ typedef struct {
   double cg_apply1_ms[2], cg_apply2_ms[2];
   /* algorithmic bytes of those launches: apply1 2nws + 12n, apply2
      6nws + (12 + s)n for a launch over w columns of s-byte scalars; with
-     panel-major CG vectors (sectors of more than 13,312 rows, 14 <= L <= 28)
-     2nws and 3nws: x is updated with p there, and no table of n is read      */
+     panel-major CG vectors (sectors of more than 13,312 rows, 14 <= L <= 28,
+     near half filling) 2nws and 3nws: x is updated with p there, and no table
+     of n is read.
+     Sectors of at most 13,312 rows run every step of a column in one
+     workgroup.  There a "launch" is a CG step, all of them are timed, the
+     milliseconds are those that a column spent in the two applies with their
+     sums (device clock, mean over the columns, which run side by side; the p
+     update is in neither), and the bytes are those of the gather kernels for
+     the columns that ran, which stay in LDS and registers: no memory rate
+     follows from them.                                                       */
   double cg_apply1_bytes[2], cg_apply2_bytes[2];
   int64_t pcg_columns;   /* CG steps times block columns, summed over inner
                             solves (fewer than pcg_steps * block with lock or
@@ -266,7 +276,8 @@ typedef struct {
   double t_apply, t_gram, t_small;
   int cg_split;          /* the timed CG steps ran the two-pass kernels      */
   /* opts.timing: every CG step of the solve (the timed ones are the first up
-     to 64 of each inner CG call, of each column chunk): launches of each CG
+     to 64 of each inner CG call, of each column chunk; all of them in sectors
+     of at most 13,312 rows): launches of each CG
      kernel, their algorithmic bytes, and their device milliseconds estimated
      per inner CG call as the timed launches' mean times its steps (the other
      steps replay the same launches from a captured graph).  [0]=FP64 [1]=FP32 */

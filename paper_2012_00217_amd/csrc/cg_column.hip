@@ -47,6 +47,12 @@ __global__ __launch_bounds__(256) void k_col_tab(const uint32_t* __restrict__ st
   while (m < kColSlots) put(n);
 }
 
+// Ticks of the device's wall clock that a column spent in its two applies (each with its
+// sum), over all launches.
+struct ColClock {
+  uint64_t apply[2];
+};
+
 template <class T>
 struct ColArgs {
   const uint4* tab;
@@ -60,6 +66,7 @@ struct ColArgs {
   T* p;
   T* x;
   PcgCoef* coef;
+  ColClock* clock;  // TIMED: per column
   int n, m, m_keep, keep;  // columns [0, keep) run m_keep steps, the others m
   double sigma, halfJ;
 };
@@ -88,8 +95,9 @@ __device__ inline double block_sum(double s, double* sw) {
 
 // K rows per thread: row = tid + k * blockDim.  LEAN (more rows than the registers
 // hold vectors for): r and T take the registers; x, p and the diagonals are read
-// and written in memory (in the L2).
-template <class T, int K, bool LEAN>
+// and written in memory (in the L2).  TIMED: a kernel of its own, since reading the clock
+// under a branch costs every call 1.4% (n = 924).
+template <class T, int K, bool LEAN, bool TIMED>
 __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ double sw[2][kColThreads / 64];
@@ -220,8 +228,10 @@ __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
     return row(k) < n ? v : (T)0;
   };
 
+  uint64_t ticks[2] = {0, 0}, mark = 0;
   for (int it = 0; it < count; ++it) {
     T t[K];
+    if constexpr (TIMED) mark = wall_clock64();
     double s = 0.0;
     renew();
     Row next = fetch(0, false);
@@ -234,6 +244,11 @@ __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
       if constexpr (K > 2) __builtin_amdgcn_sched_barrier(0);
     }
     const double pap = block_sum(s, sw[0]);  // every gather of p is done
+    if constexpr (TIMED) {
+      const uint64_t now = wall_clock64();
+      ticks[0] += now - mark;
+      mark = now;
+    }
     live = live && pap > 0.0;
     const double alpha = live ? rho / pap : 0.0;
     const T al = (T)alpha;
@@ -257,6 +272,7 @@ __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
       if constexpr (K > 2) __builtin_amdgcn_sched_barrier(0);
     }
     const double rz = block_sum(s, sw[1]);  // every gather of T is done
+    if constexpr (TIMED) ticks[1] += wall_clock64() - mark;
     live = live && rz > 0.0;
     const T be = (T)(live ? rz / rho : 0.0);
     if (live) rho = rz;
@@ -280,6 +296,9 @@ __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
     }
     __syncthreads();
   }
+  if constexpr (TIMED)
+    if (tid == 0)
+      for (int i = 0; i < 2; ++i) a.clock[c].apply[i] += ticks[i];
   const bool done = mm.flush || count == steps;
 #pragma unroll
   for (int k = 0; k < K; ++k) {
@@ -309,9 +328,10 @@ __global__ __launch_bounds__(kColThreads) void k_cg_col(ColMulti<T> mm) {
 
 template <class T, int K, bool LEAN>
 void launch_col(const ColMulti<T>& mm, int threads, size_t lds, hipStream_t s) {
-  MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_cg_col<T, K, LEAN>),
+  const auto kernel = mm.a[0].clock ? &k_cg_col<T, K, LEAN, true> : &k_cg_col<T, K, LEAN, false>;
+  MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((k_cg_col<T, K, LEAN>), dim3(mm.c0[mm.np]), dim3(threads), lds, s, mm);
+  hipLaunchKernelGGL(kernel, dim3(mm.c0[mm.np]), dim3(threads), lds, s, mm);
   MBL_CHECK_LAUNCH();
 }
 
@@ -408,9 +428,11 @@ void run_pcg_column(const std::vector<ColumnJob<T>>& jobs, hipStream_t s, PcgTim
   } guard{ev};
   if (stop)
     for (int i = 0; i < 2; ++i) MBL_HIP(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
-  if (tm) {
-    tm->init();
-    MBL_HIP(hipEventRecord(tm->ev[0], s));
+  DevBuf clockb;
+  if (tm) {  // one job: a timed call does not share launches
+    clockb.reset((size_t)wg * sizeof(ColClock), s);
+    MBL_HIP(hipMemsetAsync(clockb.get(), 0, clockb.bytes(), s));
+    mm.a[0].clock = clockb.as<ColClock>();
   }
   int from = 0, k = 0;
   do {
@@ -432,22 +454,31 @@ void run_pcg_column(const std::vector<ColumnJob<T>>& jobs, hipStream_t s, PcgTim
     }
   } while (from < most);
   if (tm) {
-    MBL_HIP(hipEventRecord(tm->ev[1], s));
+    std::vector<ColClock> clock(wg);
+    MBL_HIP(hipMemcpyAsync(clock.data(), clockb.get(), clockb.bytes(), hipMemcpyDeviceToHost, s));
     MBL_HIP(hipStreamSynchronize(s));
-    float ms = 0.f;
-    MBL_HIP(hipEventElapsedTime(&ms, tm->ev[0], tm->ev[1]));
-    // the steps' time in two equal parts, the algorithmic bytes of the two applies
-    for (const ColumnJob<T>& j : jobs) {
-      const double n = (double)j.H->n, w = n * j.b * sizeof(T);
-      const double by[2] = {2.0 * w + 12.0 * n, 6.0 * w + (12.0 + sizeof(T)) * n};
-      tm->launches_all += from;
-      for (int i = 0; i < 2; ++i) {
-        tm->launches[i] += from;
-        tm->ms[i] += 0.5 * ms;
-        tm->bytes[i] += from * by[i];
-        tm->ms_all[i] += 0.5 * ms;
-        tm->bytes_all[i] += from * by[i];
-      }
+    int dev = 0, khz = 0;
+    MBL_HIP(hipGetDevice(&dev));
+    MBL_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+    // The columns run side by side: the mean of their times.  The bytes are those that the
+    // gather kernels would move for the columns that ran; here they stay on the CU.
+    const ColumnJob<T>& j = jobs[0];
+    const double n = (double)j.H->n, nw = n * sizeof(T);
+    double ticks[2] = {0, 0}, cols = 0;  // cols: CG steps summed over the columns
+    for (int c = 0; c < wg; ++c) {
+      for (int i = 0; i < 2; ++i) ticks[i] += (double)clock[c].apply[i];
+      cols += std::min(from, c < mm.a[0].keep ? mm.a[0].m_keep : mm.a[0].m);
+    }
+    const double by[2] = {2.0 * nw * cols + 12.0 * n * from,
+                          6.0 * nw * cols + (12.0 + sizeof(T)) * n * from};
+    tm->launches_all += from;
+    for (int i = 0; i < 2; ++i) {
+      const double ms = ticks[i] / wg / std::max(1, khz);
+      tm->launches[i] += from;
+      tm->ms[i] += ms;
+      tm->bytes[i] += by[i];
+      tm->ms_all[i] += ms;
+      tm->bytes_all[i] += by[i];
     }
   }
 }

@@ -8,6 +8,8 @@ Tolerances: m <= 9 CG steps amplify rounding by less than 1e4 (FP64 to 1e-9 of t
 largest entry; FP32 to 2e-4 of the column norm).
 """
 
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -116,3 +118,35 @@ def test_sparse_sectors_keep_the_gather_kernels(L, nup, monkeypatch):
     W = H.pcg(R, 0.1, 5)
     monkeypatch.setenv("MBL_APPLY_LANE_BYTES", "64")
     assert torch.equal(W, H.pcg(R, 0.1, 5))
+
+
+@pytest.mark.parametrize("max_seconds", [0.0, 600.0])
+def test_column_cg_times_its_own_phases(max_seconds):
+    """opts.timing with one workgroup per column: the two applies are timed each by
+    itself inside the kernel, and the bytes are those of the columns that ran."""
+    L, s = 14, 8
+    H = api.Hamiltonian(L, workloads.disorder(L, 6.0, 1))
+    t0 = time.perf_counter()
+    ev, V, rs, info = H.solve(0.1, 4, 16, tol=1e-10, pcg_iters=75, guard_cg=0.4, max_iter=3,
+                              raise_on_noconv=False, timing=True, max_seconds=max_seconds)
+    wall = 1e3 * (time.perf_counter() - t0)
+    steps, cols = info["pcg_steps"], info["pcg_columns"]
+    assert cols < 16 * steps
+    assert info["cg_launches_all"][0] == info["cg_apply1_launches"][0] == steps
+    assert info["cg_apply1_bytes_all"][0] == pytest.approx(2 * H.n * s * cols + 12 * H.n * steps)
+    assert info["cg_apply2_bytes_all"][0] == pytest.approx(6 * H.n * s * cols + 20 * H.n * steps)
+    ms = [info["cg_apply1_ms_all"][0], info["cg_apply2_ms_all"][0]]
+    assert ms[0] != ms[1] and min(ms) > 0.0
+    # a gather of 3432 rows through one CU takes at least 0.1 us; both fit the solve
+    assert min(ms) >= 1e-4 * cols / 16 and sum(ms) <= wall
+
+
+@pytest.mark.parametrize("L,precision", [(12, "f64"), (13, "pcg32"), (14, "f64"), (15, "f64"),
+                                         (16, "f64"), (16, "pcg32")])
+def test_timing_the_column_cg_changes_no_bit(L, precision):
+    H = api.Hamiltonian(L, workloads.disorder(L, 6.0, 1), Sz=0.5 * (L % 2))
+    kw = dict(nev=4, block=8, tol=1e-8, precision=precision, pcg_iters=20, max_iter=2,
+              raise_on_noconv=False)
+    ev, V, rs, info = H.solve(0.1, **kw)
+    ev2, V2, rs2, info2 = H.solve(0.1, timing=True, **kw)
+    assert np.array_equal(ev, ev2) and torch.equal(V, V2) and np.array_equal(rs, rs2)
