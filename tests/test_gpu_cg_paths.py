@@ -150,3 +150,28 @@ def test_timing_the_column_cg_changes_no_bit(L, precision):
     ev, V, rs, info = H.solve(0.1, **kw)
     ev2, V2, rs2, info2 = H.solve(0.1, timing=True, **kw)
     assert np.array_equal(ev, ev2) and torch.equal(V, V2) and np.array_equal(rs, rs2)
+
+
+# 40 steps: at least 8 remain to be replayed.  Panels with 512 and 256 threads a tile (32
+# tiles a panel; 129 panels), gather kernels as a schedule in the environment selects them
+# and on a sector far from half filling, the two-pass kernels
+@pytest.mark.parametrize("L,Sz,b,dtype,env", [
+    (17, 0.5, 6, torch.float64, {}), (17, 0.5, 33, torch.float32, {}),
+    (17, 0.5, 258, torch.float64, {}), (20, -4.0, 6, torch.float64, {}),
+    (14, 0.0, 32, torch.float64, {"MBL_APPLY_LANE_BYTES": "64"}),
+    (14, 0.0, 32, torch.float32, {"MBL_APPLY_LANE_BYTES": "64"}),
+    (14, 0.0, 32, torch.float32, {"MBL_APPLY_SPLIT": "1"})])
+def test_replayed_steps_are_bitwise_direct_launches(L, Sz, b, dtype, env, monkeypatch):
+    """The captured step replayed against launches one by one, on the paths that replay;
+    the caller's own work between the calls does not disturb it."""
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    H = api.Hamiltonian(L, workloads.disorder(L, 4.0, 2), Sz=Sz)
+    R = torch.from_numpy(workloads.random_block(H.n, b, seed=11)).to(DEV, dtype)
+    monkeypatch.setenv("MBL_PCG_GRAPH", "0")
+    W_direct = H.pcg(R, 0.07, 40)
+    assert torch.isfinite(W_direct).all() and W_direct.abs().max() > 0
+    monkeypatch.setenv("MBL_PCG_GRAPH", "1")
+    for _ in range(3):
+        assert torch.equal(W_direct, H.pcg(R, 0.07, 40))
+        (R * 2).sum().item()
