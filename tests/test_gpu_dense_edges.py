@@ -79,6 +79,22 @@ def test_entropy_blocks(L, Sz, cut, nev):
             assert abs(S[j] - want) <= 1e-10
 
 
+def test_entropy_of_more_vectors_than_one_chunk_takes():
+    """L = 22 cut at 6: every block is small, and the 256 MB of a chunk hold 47 vectors, so
+    the last three come from a shorter second chunk."""
+    L, cut, nev = 22, 6, 50
+    H = api.Hamiltonian(L, workloads.disorder(L, 2.0, 0))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(L)
+    V = torch.randn(H.n, nev + 3, dtype=torch.float64, device=DEV, generator=g)[:, 2:2 + nev]
+    V = V / V.norm(dim=0)
+    S = H.entanglement_entropy(V, cut)
+    st = basis.enumerate_sector(L, L // 2)
+    for j in (0, 46, 47, 49):
+        want = observables.entanglement_entropy(V[:, j].cpu().numpy(), st, L, cut)
+        assert abs(S[j] - want) <= 1e-10
+
+
 def _block(n, p, dtype, seed, lead=0):
     """n x p block of one-digit integers (every product and sum of a Gram is exact), rows
     `lead` elements further apart than p."""
