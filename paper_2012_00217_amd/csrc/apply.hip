@@ -1212,6 +1212,7 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       return;
     }
     if (panel_usable(H, b)) {
+      // (a fused batch too: panel calls have no joint form)
       // Panels: measured no slower than the gather kernels at L = 17 to 24 for 1 to
       // 128 columns of either type (us per step, panels for gathers: L = 17, 64
       // FP64 columns 57 for 57; L = 18, 32 FP32 41 for 46; L = 20, 64 FP64 217 for 303;

@@ -149,3 +149,36 @@ def test_heterogeneous_mix_equals_alone_and_oracle():
         st, Ho = hamiltonian.sector_matrix(d["L"], k, d["J"], d["Delta"], d["h"])
         w_ref, _ = spectrum.nearest(Ho, r["sigma"], d["nev"])
         assert np.max(np.abs(r["evals"] - w_ref)) <= 1e-10
+
+
+# the gather kernels of several problems in one launch: a sector far from half filling,
+# and the small half-filled ones under a launch schedule
+@pytest.mark.parametrize("sizes,env", [([(20, -4.0)], {}),
+                                       ([(14, 0.0), (16, 0.0)], {"MBL_APPLY_LANE_BYTES": "64"})])
+def test_fused_gather_cg_is_bitwise_the_unfused(sizes, env, monkeypatch, capfd):
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    probs = []
+    for j in range(8):
+        L, Sz = sizes[j % len(sizes)]
+        probs.append({"L": L, "Sz": Sz, "h": workloads.disorder(L, 4.0 + j, 300 + j), "sigma": 0.1,
+                      "nev": 4, "block": 8, "tol": 1e-10, "max_iter": 3, "pcg_iters": 60, "seed": 7,
+                      "precision": "mixed" if j % 4 >= 2 else "f64"})
+    monkeypatch.setenv("MBL_FUSE_STATS", "1")
+    monkeypatch.setenv("MBL_FUSE_WAIT_MS", "200")
+    monkeypatch.setenv("MBL_BATCH_FUSE", "1")
+    fused = api.batch_solve(probs, concurrency=8, vectors=True)
+    m = re.search(r"fused CG: (\d+) groups, (\d+) calls", capfd.readouterr().err)
+    assert m, "no fusion statistics"
+    assert int(m.group(2)) > int(m.group(1)) > 0  # some CG calls ran together
+    monkeypatch.setenv("MBL_BATCH_FUSE", "0")
+    plain = api.batch_solve(probs, concurrency=8, vectors=True)
+    for d, a, b in zip(probs, fused, plain):
+        assert a["status"] == b["status"] and a["status"] in ("MBL_OK", "MBL_ENOCONV")
+        assert np.array_equal(a["evals"], b["evals"]) and torch.equal(a["evecs"], b["evecs"])
+        # three outer iterations from a random block: the Ritz values are H's by then
+        k = int(round(d["Sz"] + d["L"] / 2))
+        st, Ho = hamiltonian.sector_matrix(d["L"], k, 1.0, 1.0, d["h"])
+        V = a["evecs"].cpu().numpy()
+        rq = np.einsum("ij,ij->j", V, Ho @ V)
+        assert np.max(np.abs(rq - a["evals"])) <= 1e-10
