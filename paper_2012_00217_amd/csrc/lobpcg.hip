@@ -143,7 +143,7 @@ struct Stats {
 
 // Small FP64 device workspace of one solve (sizes for m = 3b).
 struct Small {
-  DevBuf M, V, w, C, Ch, T1, T2, Rinv, cw, ew, sel, cnt, K, Z, th, Zs, asel, Za;
+  DevBuf M, V, w, C, Ch, T1, Rinv, cw, ew, sel, cnt, K, Z, th, Zs, asel, Za;
   int mmax;
   Small(int b, hipStream_t s) {
     const int m = 3 * b;
@@ -155,7 +155,6 @@ struct Small {
     C.reset(mm, s);
     Ch.reset(mm, s);
     T1.reset(mm, s);
-    T2.reset(mm, s);
     Rinv.reset(mm, s);
     cw.reset(mm, s);
     ew.reset(small_eigh_work_bytes(m), s);
@@ -251,7 +250,8 @@ class Phase {
     rr(b);
   }
 
-  // Rayleigh-Ritz on span(S[:, 0:mact]); updates X, P (and HX, HP), mu.
+  // Rayleigh-Ritz on span(S[:, 0:mact]); updates X, P (and HX, HP); the Ritz values stay
+  // in sm_.w (the residual of the next step reads them there).
   void rr(int mact) {
     const int b = p_.b;
     const int64_t n = H_.n;
@@ -266,9 +266,6 @@ class Phase {
     else
       launch_gram<TB>(n, S, B_.ld, mact, HS, B_.ld, mact, M, mact, s_, p_.sign);
     small_eigh(mact, M, mact, sm_.w.as<double>(), sm_.V.as<double>(), mact, sm_.ew, s_);
-    mu_.resize(b);
-    MBL_HIP(hipMemcpyAsync(mu_.data(), sm_.w.as<double>(), b * sizeof(double),
-                           hipMemcpyDeviceToHost, s_));
     // C = V[:, 0:b]; with P and W also C^ = C with the X rows zeroed, projected off C
     // twice, orthonormalised: [X' P'] = S [C C^], and the same of HS
     double* C = sm_.C.as<double>();  // mact x 2b
@@ -521,7 +518,6 @@ class Phase {
 
   TB* X() { return B_.S[cur_].template as<TB>(); }
   int64_t ldx() const { return B_.ld; }
-  const std::vector<double>& mu() const { return mu_; }
 
  private:
   const Ham& H_;
@@ -532,7 +528,6 @@ class Phase {
   PhaseBufs<TB> B_;
   int cur_ = 0;
   int bp_ = 0;
-  std::vector<double> mu_;
   std::vector<int> locked_;  // Z columns of locked wanted pairs, most converged first
   std::vector<double> last_theta_all_;
   // host sources of small uploads: members, so that each outlives its
