@@ -2,7 +2,7 @@
 //
 // The rows that share the high configuration hi (the sites above the lowest kTileQ) are a
 // contiguous block of at most 252 rows, one tile.  A workgroup takes one tile of one
-// column slice of about 128 bytes: it stages its rows in LDS, gathers the flips inside the
+// column slice of 128 to 208 bytes: it stages its rows in LDS, gathers the flips inside the
 // low half from there, and the flips inside hi from the rows of another block, at one
 // offset for the whole tile.  Consecutive workgroups of an XCD take consecutive tiles, in
 // the order of tile_rank, so that what they gather stays in the XCD's L2.
@@ -11,8 +11,8 @@
 // us, k_apply 1675) and by the loads of the gathers where it is narrow: k_apply
 // computes every flip target, and its ragged blocks go in 8- and 4-byte lanes and a launch
 // per chunk (L = 21, 17 FP64 columns: 100 us, here 34; L = 24, 2 FP64 columns 160, here
-// 38).  Tiles of q = 9 or 11 low sites: 2 to 10 % slower; slices of 80 or 272 bytes: 40
-// and 130 %.
+// 38).  Tiles of q = 9 or 11 low sites: 2 to 10 % slower; slices of 80 or 272 bytes where
+// the rows are whole lines: 40 and 130 %.
 //
 // A row of a slice is a number of 16-byte pieces.  The last piece ends with the slice,
 // overlapping its neighbour where the width is odd (both write the same values), so that
@@ -156,7 +156,7 @@ bool launch_tile(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int6
   // whole pieces a slice; the last slice ends with the block, overlapping its neighbour
   a.W = std::min(w, ((w + nsl - 1) / nsl + VE - 1) / VE * VE);
   a.G = (a.W + VE - 1) / VE;
-  a.rcp = (1u << 18) / a.G + 1;  // exact for the at most 252 x 9 items of a tile
+  a.rcp = (1u << 18) / a.G + 1;  // exact for the at most 252 x 13 items of a tile
   a.ts = panel_sched(H, P, nsl, 1 << 20);  // one workgroup per tile
   if (a.ts.nwg == 8 << 20) return false;     // 32-bit thread numbers of a grid
   const int most = (int)H.pascal_host[kTileQ * kPascal + kTileQ / 2];
@@ -177,9 +177,19 @@ bool tile_apply(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int64
   constexpr int VE = 16 / (int)sizeof(T);
   const PanelTables& P = H.tile;
   if (!P.ok || ldx > (1 << 20)) return false;  // 32-bit byte offsets within a tile's rows
-  int64_t nsl = std::max<int64_t>(1, (w * (int64_t)sizeof(T) + 143) / 144);
+  // Slices of whole 128-byte lines where the rows are whole lines, else as few as slices of
+  // at most 208 bytes allow.  A slice that cuts lines fetches both ends of every row, so
+  // narrow ones cost the most: n = 705432, rows of 2048 bytes 1232 us (k_apply 1540, slices of
+  // 144 bytes 2450), 1280 bytes 774 (980, 1321); of 800 bytes in 4 slices 730 (834, in 6 of
+  // 144 898), 320 bytes in 2 226 (307, in 3 of 112 310), 192 bytes in one 88 (216, in 2 146).
+  // Slices of 256 bytes leave the L2 fewer rows (1024 bytes: 721, in 8 whole lines 711; 720
+  // bytes: 690, in 4 of 192 663).
+  const int64_t bytes = w * (int64_t)sizeof(T);
+  const bool lines = (reinterpret_cast<uintptr_t>(X) | (uintptr_t)(ldx * (int64_t)sizeof(T)) |
+                      (uintptr_t)bytes) % 128 == 0;
+  int64_t nsl = lines ? bytes / 128 : std::max<int64_t>(1, (bytes + 207) / 208);
   // short sectors: narrower slices, of at least 32 bytes, until the card is filled
-  while (P.ntiles * nsl < 512 && w * (int64_t)sizeof(T) >= 64 * nsl) nsl *= 2;
+  while (P.ntiles * nsl < 512 && bytes >= 64 * nsl) nsl *= 2;
   if (P.ntiles * nsl >= (1ll << 30)) return false;  // tile numbers
   return w >= VE ? launch_tile<T, VE>(H, sigma, X, ldx, Y, ldy, w, (int)nsl, s)
                  : launch_tile<T, 1>(H, sigma, X, ldx, Y, ldy, w, 1, s);

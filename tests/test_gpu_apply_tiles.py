@@ -42,6 +42,23 @@ def test_tiles_equal_the_gather(monkeypatch, L, Sz, b, pad, offset, dtype):
     assert torch.equal(Y, Z)
 
 
+# one slice to 208 bytes, then several; whole lines (with a stride or an offset that breaks
+# them); few tiles, whose slices are halved
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("L", [14, 18, 19, 20])
+@pytest.mark.parametrize("row,pad,offset", [(192, 0, 0), (208, 0, 0), (216, 0, 0), (320, 0, 0),
+                                            (400, 8, 8), (624, 0, 0), (632, 0, 0), (800, 0, 0),
+                                            (1152, 0, 0), (1152, 128, 0), (1152, 128, 32),
+                                            (1152, 24, 0), (2048, 0, 0), (2040, 8, 8)])
+def test_slices_equal_the_gather(monkeypatch, L, row, pad, offset, dtype):
+    es = torch.finfo(dtype).bits // 8
+    H = api.Hamiltonian(L, workloads.disorder(L, 4.0, 2), Sz=0.5 * (L % 2), Delta=0.7)
+    g = torch.Generator(device=DEV).manual_seed(L * 100 + row)
+    big = torch.randn(H.n, (row + pad) // es, generator=g, dtype=dtype, device=DEV)
+    Y, Z = _both(monkeypatch, H, big[:, offset // es:(offset + row) // es], 0.3)
+    assert torch.equal(Y, Z)
+
+
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 def test_tiles_write_their_columns_only(monkeypatch, dtype):
     L, b = 16, 19
