@@ -51,9 +51,9 @@ struct Mfma<float> {
 // consecutive columns of the row-major blocks.
 //
 // The rows are consumed in slabs of 32: the workgroup stages the slab's
-// 32 x 64 panels of A and B in LDS (16-byte loads when the blocks are aligned,
-// each element read from memory once per workgroup), and the next slab's
-// loads are in flight while the waves run their 32 MFMAs on the current one.
+// 32 x 64 panels of A and B in LDS (16-byte loads, each element read from memory
+// once per workgroup), and the next slab's loads are in flight while the waves
+// run their 32 MFMAs on the current one.
 // sym (A = B, p = q): only the tiles on and above the diagonal are formed;
 // they are enumerated row by row, and a diagonal tile stages one panel.
 constexpr int kSlab = 32;
@@ -65,14 +65,14 @@ struct GramStage {
   static constexpr int SWZ = sizeof(T) == 8 ? 1 : 3;
   // Place of element (r, c) of a panel: the rows are 64 elements apart and their blocks
   // of 16 columns are exchanged, so that the 4 rows x 16 columns of an operand read lie
-  // in different banks (FP32 103 -> 98 us at n = 184756, p = q = 192, against rows
-  // padded by 16 bytes; FP64 176 -> 174).
+  // in different banks (A^T A, n = 184756, p = 192: FP32 96 us a call, with rows padded by
+  // 16 bytes 103; FP64 161 and 168).
   __device__ static int at(int r, int c) { return r * 64 + (c ^ ((r & SWZ) << 4)); }
 };
 
 template <class T>
 __device__ inline void gram_load(const T* __restrict__ X, int64_t ldx, int ncol, int col0,
-                                 int64_t k, int64_t ke, bool vec, T (&reg)[GramStage<T>::PER][GramStage<T>::VE]) {
+                                 int64_t k, int64_t ke, T (&reg)[GramStage<T>::PER][GramStage<T>::VE]) {
   using S = GramStage<T>;
 #pragma unroll
   for (int u = 0; u < S::PER; ++u) {
@@ -80,8 +80,11 @@ __device__ inline void gram_load(const T* __restrict__ X, int64_t ldx, int ncol,
     const int r = e >> 6, c = e & 63;
     const int64_t row = k + r;
     const int col = col0 + c;
-    if (vec && row < ke && col + S::VE <= ncol) {
-      typedef T vec_t __attribute__((ext_vector_type(GramStage<T>::VE)));
+    if (row < ke && col + S::VE <= ncol) {
+      // 16 bytes at the alignment of an element: unaligned rows take the same loads
+      // (n = 184756, element by element: FP32 101 and 64 columns 72 us a call, now 44; FP64
+      // 127 columns 151, now 95)
+      typedef T vec_t __attribute__((ext_vector_type(GramStage<T>::VE), aligned(sizeof(T))));
       const vec_t v = *reinterpret_cast<const vec_t*>(X + row * ldx + col);
 #pragma unroll
       for (int t = 0; t < S::VE; ++t) reg[u][t] = v[t];
@@ -106,16 +109,17 @@ __device__ inline void gram_store(T* __restrict__ sm, const T (&reg)[GramStage<T
 }
 
 // Bound by the waits of a slab's loads and barriers: 65 % of the time the matrix cores
-// are busy.  Four workgroups per CU (launch_bounds caps the registers at 128) hold all
-// 1024 workgroups of a launch at once; at 152 registers three fitted, and the last
-// quarter of the workgroups ran as a second round (n = 184756, p = q = 192, FP64:
-// 275 us, now 203; p = 128, q = 64: 110, now 80; FP32 131, now 108).
+// are busy.  Four workgroups per CU (FP64: launch_bounds caps the registers at 128) hold
+// all 1024 workgroups of a launch at once; at 152 registers three fit, and the last
+// quarter of the workgroups runs as a second round (n = 184756, a call: A^T A of 192
+// columns 161 us, without the cap 219; 128 and 64 columns 72 and 80).  FP32 takes 64
+// registers without a cap, and is slower with one (n = 705432, 96 and 48 columns: 130 us,
+// capped 145).
 template <class T>
-__global__ __launch_bounds__(256, 4) void k_gram(int64_t n, const T* __restrict__ A, int64_t lda,
-                                                 int p, const T* __restrict__ B, int64_t ldb,
-                                                 int q, int sym, int vec, int tiles,
-                                                 int64_t rows_per_split,
-                                                 double* __restrict__ part) {
+__global__ __launch_bounds__(256, sizeof(T) == 8 ? 4 : 1)
+void k_gram(int64_t n, const T* __restrict__ A, int64_t lda, int p, const T* __restrict__ B,
+            int64_t ldb, int q, int sym, int tiles, int64_t rows_per_split,
+            double* __restrict__ part) {
   using M = Mfma<T>;
   using S = GramStage<T>;
   __shared__ T sa[kSlab * 64], sb[kSlab * 64];
@@ -153,8 +157,8 @@ __global__ __launch_bounds__(256, 4) void k_gram(int64_t n, const T* __restrict_
     for (int j = 0; j < 2; ++j) acc[i][j] = typename M::acc{0, 0, 0, 0};
   T ra[S::PER][S::VE], rb[S::PER][S::VE];
   if (kb < ke) {
-    gram_load<T>(A, lda, p, ty * 64, kb, ke, vec != 0, ra);
-    if (!same) gram_load<T>(B, ldb, q, tx * 64, kb, ke, vec != 0, rb);
+    gram_load<T>(A, lda, p, ty * 64, kb, ke, ra);
+    if (!same) gram_load<T>(B, ldb, q, tx * 64, kb, ke, rb);
   }
   for (int64_t k = kb; k < ke; k += kSlab) {
     __syncthreads();  // the previous slab's MFMAs are done with the LDS panels
@@ -162,8 +166,8 @@ __global__ __launch_bounds__(256, 4) void k_gram(int64_t n, const T* __restrict_
     if (!same) gram_store<T>(sb, rb);
     __syncthreads();
     if (k + kSlab < ke) {
-      gram_load<T>(A, lda, p, ty * 64, k + kSlab, ke, vec != 0, ra);
-      if (!same) gram_load<T>(B, ldb, q, tx * 64, k + kSlab, ke, vec != 0, rb);
+      gram_load<T>(A, lda, p, ty * 64, k + kSlab, ke, ra);
+      if (!same) gram_load<T>(B, ldb, q, tx * 64, k + kSlab, ke, rb);
     }
     if (below) continue;
 #pragma unroll
@@ -443,12 +447,8 @@ void launch_gram_part(const GramPlan& g, int64_t n, const T* A, int64_t lda, int
                       double scale) {
   if (p == 0 || q == 0) return;
   PhaseTick tick(PhaseClock::GRAM, s);
-  const uintptr_t align = reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) |
-                          (uintptr_t)(lda * (int64_t)sizeof(T)) |
-                          (uintptr_t)(ldb * (int64_t)sizeof(T));
-  const int vec = (align % 16) == 0;
   hipLaunchKernelGGL(k_gram<T>, dim3((unsigned)(g.tiles * g.splits)), dim3(256), 0,
-                     s, n, A, lda, p, B, ldb, q, g.sym, vec, g.tiles, g.rows, part);
+                     s, n, A, lda, p, B, ldb, q, g.sym, g.tiles, g.rows, part);
   MBL_CHECK_LAUNCH();
   hipLaunchKernelGGL(k_gram_fold, dim3((unsigned)(((int64_t)p * q + 15) / 16)), dim3(256), 0, s,
                      part, (int)g.splits, p, q, g.sym, scale, C, ldc);

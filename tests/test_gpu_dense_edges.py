@@ -118,6 +118,19 @@ def test_gram_edges(n, p, q, lead, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n", [33, 1000])
+@pytest.mark.parametrize("p,q", [(3, 2), (17, 5), (64, 64), (67, 33)])
+def test_gram_of_unaligned_columns(n, p, q, dtype):
+    """Operands that begin one element into a row, one of them or both, up to the last
+    element of their storage."""
+    a, b = _block(n, p + 1, dtype, 1), _block(n, q + 1, dtype, 2)
+    A, B = a[:, 1:], b[:, 1:]
+    assert torch.equal(api.gram(A, B), A.double().T.contiguous() @ B.double())
+    assert torch.equal(api.gram(A, b), A.double().T.contiguous() @ b.double())
+    assert torch.equal(api.gram(A, A), A.double().T.contiguous() @ A.double())
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("p", [15, 16, 31, 32, 33, 63, 64, 65, 96, 97, 192, 200])
 def test_gram_of_one_operand_is_that_of_two(p, dtype):
     """Mirrored tiles and skipped quadrants against the full product, rounding and all."""
