@@ -7,11 +7,13 @@
 //    each writes an FP64 partial tile and a second kernel folds the partials
 //    in split order, so the result is bitwise reproducible.
 //  * Block combination Y = A C + beta Y with a small FP64 coefficient matrix
-//    C (rounded to the block type), register-tiled through LDS.
+//    C (rounded to the block type) on the matrix cores: the rows of A straight into the
+//    operand registers, C in LDS.
 //  * Precision conversion and the counter-based random starting block.
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "common.h"
 
@@ -237,29 +239,38 @@ __global__ __launch_bounds__(256) void k_gram_fold(const double* __restrict__ pa
 // tiles without a barrier.
 //
 // Bound by memory (378 MB) and the matrix cores (4.5 GFLOP FP64) about equally at
-// n = 184756, 192 -> 64 columns: 137 us a call; the vector-unit form that staged A through
-// LDS took 237.  64 -> 64: 88, now 48; FP32 192 -> 64: 131, now 78.
+// n = 184756, 192 -> 64 columns: 99 us a call; a vector-unit form that stages A through
+// LDS takes 207.  FP32: 65 and 114.  Full slabs are read without a mask (with one: FP64 122,
+// FP32 73) and at the alignment of an element, so that unaligned rows take the same loads
+// (FP32 150 -> 75: 82 us, element by element 119).
+//
+// Registers: FP32 with 32 columns takes 135 without the cap, and of the two workgroups of 8
+// wavefronts that a CU is to hold only one fits (32 -> 32: 20.8 us, now 17.8; 96 -> 32: 34.6
+// and 28.5).
 template <class T>
 struct CombineStage {
   static constexpr int VE = 16 / (int)sizeof(T);  // elements per 16-byte piece
   static constexpr int SL = 4 * VE;               // k per slab
   static constexpr int GK = 4 * SL;               // k per group
-  // Place of C[k][c] in a chunk of rows of W elements: the 4 rows of an operand, VE apart,
-  // go to different banks.
-  template <int W>
+  // Place of C[k][c] in a chunk: the 4 rows of an operand, VE apart, go to different
+  // banks.  Rows of 48 are padded, the others exchange their blocks of 16.
+  static constexpr int row(int nb) { return nb == 3 ? 48 + 16 / VE : 16 * nb; }
+  template <int NB>
   __device__ static int at(int k, int c) {
-    constexpr int M = (sizeof(T) == 8 ? 2 : 4) < W / 16 ? (sizeof(T) == 8 ? 2 : 4) : W / 16;
-    return k * W + (c ^ (((k / VE) & (M - 1)) << 4));
+    if constexpr (NB == 3) {
+      return k * row(NB) + c;
+    } else {
+      constexpr int M = (sizeof(T) == 8 ? 2 : 4) < NB ? (sizeof(T) == 8 ? 2 : 4) : NB;
+      return k * row(NB) + (c ^ (((k / VE) & (M - 1)) << 4));
+    }
   }
 };
 
 template <class T, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* A, int64_t lda, int p,
-                                                     const double* __restrict__ Cm, int64_t ldc,
-                                                     T* Y, int64_t ldy, int q, double beta,
-                                                     double scale,
-                                                     const double* __restrict__ colscale, int vec,
-                                                     int kc, int64_t tiles) {
+__global__ __launch_bounds__(64 * NW, NB == 2 ? 4 : 1)
+void k_combine(int64_t n, const T* A, int64_t lda, int p, const double* __restrict__ Cm,
+               int64_t ldc, T* Y, int64_t ldy, int q, double beta, double scale,
+               const double* __restrict__ colscale, bool vec, int kc, int64_t tiles) {
   using M = Mfma<T>;
   using S = CombineStage<T>;
   constexpr int VE = S::VE, SL = S::SL, GK = S::GK, W = 16 * NB;
@@ -270,14 +281,17 @@ __global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* A, int6
   const int c0 = blockIdx.y * W;
   const int64_t stride = (int64_t)gridDim.x * NW;
   typedef T vec_t __attribute__((ext_vector_type(VE)));
+  typedef T mem_t __attribute__((ext_vector_type(VE), aligned(sizeof(T))));  // in memory
 
   auto fetch = [&](vec_t (&reg)[4], int64_t tile, int k0) {
     const T* src = A + min(tile * 16 + li, n - 1) * lda;  // rows beyond n are not stored
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int k = k0 + u * SL + lk * VE;
-      if (vec) {  // p is a multiple of VE
-        const vec_t v = *reinterpret_cast<const vec_t*>(src + (k < p ? k : 0));
+      if (k0 + (u + 1) * SL <= p) {
+        reg[u] = *reinterpret_cast<const mem_t*>(src + k);
+      } else if (vec) {  // p is a multiple of VE
+        const vec_t v = *reinterpret_cast<const mem_t*>(src + (k < p ? k : 0));
 #pragma unroll
         for (int t = 0; t < VE; ++t) reg[u][t] = k < p ? v[t] : (T)0;
       } else {
@@ -305,7 +319,7 @@ __global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* A, int6
         for (int e = threadIdx.x; e < kc * W; e += 64 * NW) {
           const int k = e / W, c = e % W;
           const double cscale = colscale && c0 + c < q ? scale * colscale[c0 + c] : scale;
-          Cs[S::template at<W>(k, c)] =
+          Cs[S::template at<NB>(k, c)] =
               (k0 + k < p && c0 + c < q) ? (T)(Cm[(int64_t)(k0 + k) * ldc + c0 + c] * cscale) : (T)0;
         }
         __syncthreads();
@@ -325,7 +339,7 @@ __global__ __launch_bounds__(64 * NW) void k_combine(int64_t n, const T* A, int6
           T b[NB];
 #pragma unroll
           for (int j = 0; j < NB; ++j)
-            b[j] = Cs[S::template at<W>(kl + u * SL + lk * VE + t, 16 * j + li)];
+            b[j] = Cs[S::template at<NB>(kl + u * SL + lk * VE + t, 16 * j + li)];
 #pragma unroll
           for (int j = 0; j < NB; ++j) acc[j] = M::op(cur[u][t], b[j], acc[j]);
         }
@@ -493,8 +507,38 @@ double* gram_scratch() {
   return g_scratch[dev];
 }
 
-bool combine_wide(int64_t n, int q) {
-  return q > 32 && (n >= 32768 || q > 32 * 65535);  // second: blocks of a grid
+// Shapes of a combination: blocks of 16 columns per wavefront, wavefronts per workgroup.
+struct CombineShape {
+  int nb, nw;
+};
+
+// Wide: all 64 columns in one wavefront read A once, and 16 wavefronts share a C of up to 96
+// KB (192 -> 64 columns, n = 184756, FP64, with masked loads: 122 us a call, in two blocks of
+// 32 columns 135).
+// Narrow: no work on absent columns, and for short sectors less C per workgroup and more
+// workgroups (n = 3432, 192 -> 64, FP32: 12 us, wide 26).
+//
+// FP32 takes half the time a row, so what a short sector leaves idle shows (us a call, tiles
+// of 16 rows on 256 CUs):
+//  * up to 64 columns and 2048 tiles: one round of 8 wavefronts a workgroup (n = 24310, 192 ->
+//    64: 18, narrow 23, wide 26);
+//  * to 3072 tiles 3 workgroups of 4 are more even than 2 of 8 or 1 of 16 (n = 48620, 64 -> 64:
+//    13.4, 16.5, 14.9), while C is short (192 -> 64: 33.7, wide 31.4);
+//  * beyond one round of 16, to 6144 tiles, 8 (n = 92378, 64 -> 64: 21.1, wide 22.8);
+//  * blocks of 48 columns where they are as few as blocks of 64 (n = 48620, 64 -> 36: 11.7,
+//    wide 14.5; 96 -> 96: 24 and 31; n = 184756, 150 -> 75: 82 and 110).
+template <class T>
+CombineShape combine_shape(int64_t n, int p, int q) {
+  if (q > 32 * 65535) return {4, 16};  // blocks of a grid
+  if (q <= 32) return {2, 8};
+  if (sizeof(T) == 4 && n > 16384) {
+    const int64_t tiles = (n + 15) / 16;
+    if (q <= 64 && tiles <= 2048) return {4, 8};
+    if ((q + 47) / 48 == (q + 63) / 64) return {3, 16};
+    if (q <= 64 && tiles <= 3072 && p <= 128) return {4, 4};
+    if (q <= 64 && tiles > 4096 && tiles <= 6144) return {4, 8};
+  }
+  return n >= 32768 ? CombineShape{4, 16} : CombineShape{2, 8};
 }
 
 template <class T, int NB, int NW>
@@ -504,23 +548,22 @@ void launch_combine_as(int64_t n, const T* A, int64_t lda, int p, const double* 
   using S = CombineStage<T>;
   constexpr size_t kLds = 96 * 1024;  // p = 192 of 64 FP64 columns in one chunk
   constexpr int W = 16 * NB;
-  const int kc = (int)std::min<int64_t>(kLds / (W * sizeof(T)),
+  constexpr size_t row = S::row(NB) * sizeof(T);
+  const int kc = (int)std::min<int64_t>(kLds / row / S::GK * S::GK,
                                         std::max<int64_t>(1, (p + S::GK - 1) / S::GK) * S::GK);
-  const size_t lds = (size_t)kc * W * sizeof(T);
+  const size_t lds = kc * row;
   const int64_t tiles = (n + 15) / 16;
   const int64_t cols = (q + W - 1) / W;
   // as many workgroups as are resident at once: each loads C once
   const int64_t per_cu = std::min<int64_t>(16 / NW, (160 * 1024) / (int64_t)lds);
   const int64_t grid = std::min<int64_t>((tiles + NW - 1) / NW,
                                          std::max<int64_t>(1, 256 * per_cu / cols));
-  const uintptr_t align = reinterpret_cast<uintptr_t>(A) | (uintptr_t)(lda * (int64_t)sizeof(T)) |
-                          (uintptr_t)((int64_t)p * (int64_t)sizeof(T));
   if (lds > 64 * 1024)
     MBL_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_combine<T, NB, NW>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL((k_combine<T, NB, NW>), dim3((unsigned)grid, (unsigned)cols), dim3(64 * NW),
                      lds, s, n, A, lda, p, C, ldc, Y, ldy, q, beta, scale,
-                     colscale, (align % 16) == 0 ? 1 : 0, kc, tiles);
+                     colscale, p % S::VE == 0, kc, tiles);
   MBL_CHECK_LAUNCH();
 }
 
@@ -529,20 +572,32 @@ void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, 
                     int64_t ldy, int q, double beta, hipStream_t s, double scale,
                     const double* colscale) {
   if (n == 0 || q == 0) return;
-  // Wide: all 64 columns in one wavefront read A once, and 16 wavefronts share a C of up to
-  // 96 KB (192 -> 64 columns, n = 184756, FP64: 137 us, two blocks of 32 columns 150).
-  // Narrow: no work on absent columns (51 -> 17, n = 705432: 115 us, wide 143), and for
-  // short sectors less C per workgroup and more workgroups (96 -> 32, n = 3432: 13 us,
-  // wide 23).
-  if (combine_wide(n, q))
-    launch_combine_as<T, 4, 16>(n, A, lda, p, C, ldc, Y, ldy, q, beta, scale, colscale, s);
-  else
-    launch_combine_as<T, 2, 8>(n, A, lda, p, C, ldc, Y, ldy, q, beta, scale, colscale, s);
+  const CombineShape f = combine_shape<T>(n, p, q);
+  auto run = [&](auto nb, auto nw) {
+    launch_combine_as<T, decltype(nb)::value, decltype(nw)::value>(n, A, lda, p, C, ldc, Y, ldy, q,
+                                                                   beta, scale, colscale, s);
+  };
+  using I2 = std::integral_constant<int, 2>;
+  using I4 = std::integral_constant<int, 4>;
+  using I8 = std::integral_constant<int, 8>;
+  using I16 = std::integral_constant<int, 16>;
+  if (f.nb == 2) return run(I2{}, I8{});
+  if constexpr (sizeof(T) == 4) {
+    if (f.nb == 3) return run(std::integral_constant<int, 3>{}, I16{});
+    if (f.nw == 4) return run(I4{}, I4{});
+    if (f.nw == 8) return run(I4{}, I8{});
+  }
+  run(I4{}, I16{});
 }
 
 // One block of columns: a wavefront has read its 16 rows of A when it writes them, and no
 // other reads them (rows read ahead beyond the end are not used).
-bool combine_in_place(int64_t n, int q) { return q <= (combine_wide(n, q) ? 64 : 32); }
+template <class T>
+bool combine_in_place(int64_t n, int p, int q) {
+  return q <= 16 * combine_shape<T>(n, p, q).nb;
+}
+template bool combine_in_place<double>(int64_t, int, int);
+template bool combine_in_place<float>(int64_t, int, int);
 
 template <class T>
 void launch_residual(int64_t n, int b, const T* A, int64_t lda, double sign, const T* X,

@@ -410,7 +410,8 @@ void launch_combine(int64_t n, const T* A, int64_t lda, int p, const double* C, 
                     int64_t ldy, int q, double beta, hipStream_t s, double scale = 1.0,
                     const double* colscale = nullptr);
 // Y may be A (ldy = lda): every wavefront reads the rows that it writes, all of them first.
-bool combine_in_place(int64_t n, int q);
+template <class T>
+bool combine_in_place(int64_t n, int p, int q);
 // R = sign A - X diag(mu), mu on the device; A may be R.
 template <class T>
 void launch_residual(int64_t n, int b, const T* A, int64_t lda, double sign, const T* X,

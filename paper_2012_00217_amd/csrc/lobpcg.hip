@@ -219,7 +219,7 @@ class Phase {
       const int k = chol_drop(q, sm_.T1.as<double>(), q, drop_tol<TB>(), sm_.Rinv.as<double>(),
                               sm_.cw.as<double>(), sm_.cnt.as<int>(), s_);
       // Rinv is q x q with ld q, first k columns meaningful
-      if (combine_in_place(H_.n, k)) {
+      if (combine_in_place<TB>(H_.n, q, k)) {
         launch_combine<TB>(H_.n, X, ldx, q, sm_.Rinv.as<double>(), q, X, ldx, k, 0.0, s_);
         q = k;
         continue;

@@ -160,6 +160,30 @@ def test_block_combine_edges(n, p, q, lead, dtype):
     assert torch.equal(Y.double(), A.double() @ Cm)
 
 
+# FP32 shapes by tiles of 16 rows (1024, 2048, 3072, 4096, 6144 of them) and blocks of 48 or
+# 64 columns; rows of A at any alignment, up to the last element of their storage
+@pytest.mark.parametrize("n", [16384, 16385, 32768, 32769, 49152, 49153, 65537, 98305])
+@pytest.mark.parametrize("p,q", [(64, 64), (33, 33), (75, 41), (130, 65), (96, 96), (150, 96),
+                                 (192, 64), (600, 48), (1030, 50)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_block_combine_fp32_shapes(n, p, q, offset):
+    A = _block(n, p + offset, torch.float32, 3)[:, offset:]
+    Cm = _block(p, q, torch.float64, 4)
+    assert torch.equal(api.block_combine(A, Cm).double(), A.double() @ Cm)
+
+
+@pytest.mark.parametrize("b", [33, 48, 64])
+def test_orthonormalisation_in_place_of_fp32_blocks(b):
+    """Mixed solves of a sector in each shape's range orthonormalise their FP32 blocks in
+    place: the pairs are H's."""
+    for L, Sz in ((17, 2.5), (17, 0.5), (18, 0.0)):
+        H = api.Hamiltonian(L, workloads.disorder(L, 6.0, 1), Sz=Sz)
+        ev, V, rs, info = H.solve(0.1, 4, b, tol=1e-9, precision="mixed", pcg_iters=120)
+        _, Ho = hamiltonian.sector_matrix(L, basis.nup_from_sz(L, Sz), 1.0, 1.0,
+                                          workloads.disorder(L, 6.0, 1))
+        assert np.all(linalg.residual_norms(Ho, ev, V.cpu().numpy()) <= 1e-9)
+
+
 def test_block_combine_keeps_non_finite_rows_apart():
     """Padding rows, columns and slabs take nothing from their neighbours."""
     A = torch.ones(40, 5, dtype=torch.float64, device=DEV)
