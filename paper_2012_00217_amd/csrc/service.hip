@@ -37,11 +37,13 @@ using clk = std::chrono::steady_clock;
 
 size_t footprint(int64_t n, int b, int prec) {
   // LOBPCG: S and HS double-buffered (4 x 3b columns), residual and scratch
-  // (2b), starting block and eigenvectors (2b, FP64); PCG: r, p, T (3b) plus
-  // the converted right-hand side and solution (2b) when the PCG runs in a
-  // narrower type; per row: state (4 B), diagonal (8 B), Jacobi (8 B).
+  // (2b), starting block and eigenvectors (2b, FP64); PCG: r, p, T (3b, in
+  // whole panels of 16 bytes a row) plus the converted right-hand side and
+  // solution (2b) when the PCG runs in a narrower type; per row: state (4 B),
+  // diagonal (8 B), Jacobi (8 B).
   auto phase = [&](int sb, int sp) {
-    double cols = 14.0 * b * sb + 3.0 * b * sp + (sb != sp ? 2.0 * b * sp : 0.0);
+    const double panels = (b * sp + 15) / 16 * 16;
+    double cols = 14.0 * b * sb + 3.0 * panels + (sb != sp ? 2.0 * b * sp : 0.0);
     return cols + 16.0 * b + 20.0;
   };
   double per_row = 0;

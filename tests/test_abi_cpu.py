@@ -104,3 +104,17 @@ def test_eigensolver_workspace_serves_every_smaller_size(lib):
     assert all(a <= b for a, b in zip(sizes, sizes[1:]))
     # 30 sweeps of 191 rounds of 96 rotations, their count and 192 column places
     assert sizes[191] >= 30 * 191 * 96 * 16 + 193 * 4
+
+
+@pytest.mark.parametrize("block", [1, 2, 3, 5, 32])
+def test_footprint_counts_whole_panels_of_the_cg(block):
+    """The CG of a large half-filled sector keeps r, p and T in panels of 16 bytes a row,
+    which narrow blocks do not fill."""
+    from paper_2012_00217_amd import api
+    n, rows = 40116600, lambda s: 16 * -(-block * s // 16)
+    # during a CG call: S, HS, residual, scratch and eigenvector columns, the CG's three
+    # vectors (and in FP32 the converted residual and solution), state, diagonal, Jacobi
+    f64 = n * (14 * 8 * block + 8 + 3 * rows(8) + 20)
+    pcg32 = n * (14 * 8 * block + 8 + 3 * rows(4) + 2 * 4 * block + 16)
+    assert api.footprint_bytes(28, block, "f64") >= f64
+    assert api.footprint_bytes(28, block, "pcg32") >= pcg32
