@@ -1193,7 +1193,7 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
   if (n == 0 || b == 0) return;
   const int wc = pcg_chunk_width<T>(n, b);
   if (wc == b && !gather_forced()) {
-    if (H.col_ok) {
+    if (H.col_ok && column_grid_fits(n, b)) {
       // One workgroup per column: every sector whose vector fits the LDS.  Per CG
       // step, against the best of the other two: 3.3 for 24 us (L = 12, 16 FP64
       // columns), 5.7 for 28 (L = 14, 32 FP64), 14.8 for 30 (L = 16, 32 FP32); 32 for 33
@@ -1211,7 +1211,7 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       }
       return;
     }
-    if (panel_usable(H, b)) {
+    if (panel_usable<T>(H, b)) {
       // (a fused batch too: panel calls have no joint form)
       // Panels: measured no slower than the gather kernels at L = 17 to 24 for 1 to
       // 128 columns of either type (us per step, panels for gathers: L = 17, 64

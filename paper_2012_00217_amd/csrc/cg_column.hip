@@ -335,6 +335,10 @@ void launch_col(const ColMulti<T>& mm, int threads, size_t lds, hipStream_t s) {
   MBL_CHECK_LAUNCH();
 }
 
+int column_threads(int64_t n) {
+  return n <= kColThreads ? (int)((n + 63) / 64 * 64) : kColThreads;
+}
+
 // Largest sector: 13 rows per thread (L = 16), which is also what LDS holds of FP64.
 constexpr int kColMaxRows = 13 * kColThreads;
 static_assert((kColMaxRows + 1) * sizeof(double) <= (156 << 10) && 4 * kColMaxRows < 65536,
@@ -352,6 +356,8 @@ void build_column_tables(Ham& H, hipStream_t s) {
                      H.col_tab.as<uint16_t>());
   MBL_CHECK_LAUNCH();
 }
+
+bool column_grid_fits(int64_t n, int64_t b) { return b * column_threads(n) < (1ll << 32); }
 
 // One CG of each job, all with the same number of rows per thread, in shared launches.
 template <class T>
@@ -405,7 +411,7 @@ void run_pcg_column(const std::vector<ColumnJob<T>>& jobs, hipStream_t s, PcgTim
   }
   mm.c0[mm.np] = wg;
   const size_t lds = ((size_t)nmax + 1) * sizeof(T);
-  const int threads = rows == 1 ? (int)((nmax + 63) / 64 * 64) : kColThreads;
+  const int threads = column_threads(nmax);
   auto launch = [&]() {
     if (rows <= 1)
       launch_col<T, 1, false>(mm, threads, lds, s);

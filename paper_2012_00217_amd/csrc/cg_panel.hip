@@ -710,8 +710,8 @@ void build_panel_tables(Ham& H, hipStream_t s) {
   MBL_CHECK_LAUNCH();
 }
 
-bool panel_usable(const Ham& H, int b) {
-  return H.panel.ok && (int64_t)H.panel.ntiles * ((b + 1) / 2) < (1ll << 30);  // tile numbers
+bool panel_grid_fits(int64_t tiles, int64_t panels) {
+  return panels <= 65535 && tiles * panels < (1ll << 30);
 }
 
 namespace {

@@ -341,7 +341,13 @@ PanelSched panel_sched(const Ham& H, const PanelTables& P, int npan, int slots);
 template <class T>
 bool tile_apply(const Ham& H, double sigma, const T* X, int64_t ldx, T* Y, int64_t ldy, int w,
                 hipStream_t s);
-bool panel_usable(const Ham& H, int b);
+// Its launches take that many panels (tile numbers, blocks of a grid in y).
+bool panel_grid_fits(int64_t tiles, int64_t panels);
+template <class T>
+bool panel_usable(const Ham& H, int b) {
+  constexpr int VE = 16 / (int)sizeof(T);
+  return H.panel.ok && panel_grid_fits(H.panel.ntiles, ((int64_t)b + VE - 1) / VE);
+}
 template <class T>
 void run_pcg_panel(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, T* W,
                    int64_t ldw, int b, int m, hipStream_t s, PcgTiming* tm, const StopCheck* stop,
@@ -361,6 +367,8 @@ struct ColumnJob {
   int b, m, keep, m_keep;
 };
 void build_column_tables(Ham& H, hipStream_t s);
+// One launch takes b columns (32-bit thread numbers of a grid).
+bool column_grid_fits(int64_t n, int64_t b);
 template <class T>
 void run_pcg_column(const std::vector<ColumnJob<T>>& jobs, hipStream_t s, PcgTiming* tm,
                     const StopCheck* stop);

@@ -118,3 +118,16 @@ def test_footprint_counts_whole_panels_of_the_cg(block):
     pcg32 = n * (14 * 8 * block + 8 + 3 * rows(4) + 2 * 4 * block + 16)
     assert api.footprint_bytes(28, block, "f64") >= f64
     assert api.footprint_bytes(28, block, "pcg32") >= pcg32
+
+
+def test_cg_launches_fit_a_grid(lib):
+    """The CG paths leave a block with more columns than a launch takes to the gather
+    kernels: 2^32 threads, 65,535 blocks in y, 2^30 tiles."""
+    col = lib._ZN3mbl16column_grid_fitsEll  # mbl::column_grid_fits(n, b)
+    pan = lib._ZN3mbl15panel_grid_fitsEll  # mbl::panel_grid_fits(tiles, panels)
+    for f in (col, pan):
+        f.restype, f.argtypes = C.c_bool, [C.c_int64, C.c_int64]
+    assert col(924, 16) and col(13312, (1 << 22) - 1) and not col(13312, 1 << 22)
+    assert col(2, (1 << 26) - 1) and not col(2, 1 << 26)  # one wavefront a column
+    assert pan(32, 65535) and not pan(32, 65536)
+    assert pan(1 << 16, (1 << 14) - 1) and not pan(1 << 16, 1 << 14)
