@@ -167,7 +167,14 @@ void entropy_small_blocks(const Ham& H, const double* V, int64_t ldv, int nev, i
   std::copy_n(reinterpret_cast<const char*>(blocks.data()), at_i - at_b, up.data() + at_b);
   std::copy_n(reinterpret_cast<const char*>(items.data()), up.size() - at_i, up.data() + at_i);
   const size_t head = (up.size() + 255) / 256 * 256;
-  DevBuf buf(head + (size_t)chunk * (H.n + gsum + wsum) * sizeof(double), s);
+  DevBuf buf;
+  try {
+    buf.reset(head + (size_t)chunk * (H.n + gsum + wsum) * sizeof(double), s);
+  } catch (const Error& e) {
+    if (e.status != MBL_ENOMEM) throw;
+    (void)hipGetLastError();
+    return;  // block by block, which needs no copy of the vectors
+  }
   char* base = buf.as<char>();
   double* psi = reinterpret_cast<double*>(base + head);
   double* G = psi + (size_t)chunk * H.n;

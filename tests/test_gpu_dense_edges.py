@@ -79,6 +79,31 @@ def test_entropy_blocks(L, Sz, cut, nev):
             assert abs(S[j] - want) <= 1e-10
 
 
+def test_entropy_without_memory_for_a_copy_of_the_vectors():
+    """The joint launches keep the vectors by columns; where the allocator has no room for
+    that, each block is taken by itself."""
+    L, nev = 12, 16
+    H = api.Hamiltonian(L, workloads.disorder(L, 2.0, 0))
+    V = torch.from_numpy(workloads.random_block(H.n, nev, seed=3)).to(DEV)
+    V = V / V.norm(dim=0)
+    want = H.entanglement_entropy(V)
+    refused = []
+
+    def alloc(n, s):
+        if n > 128 << 10:
+            refused.append(n)
+            return 0
+        return torch._C._cuda_cudaCachingAllocator_raw_alloc(int(n), int(s or 0))
+
+    api.use_allocator(alloc, lambda p, s: torch._C._cuda_cudaCachingAllocator_raw_delete(int(p)))
+    try:
+        got = H.entanglement_entropy(V)
+    finally:
+        api.use_torch_allocator()
+    assert refused
+    np.testing.assert_allclose(got, want, rtol=0, atol=1e-12)
+
+
 def test_entropy_of_more_vectors_than_one_chunk_takes():
     """L = 22 cut at 6: every block is small, and the 256 MB of a chunk hold 47 vectors, so
     the last three come from a shorter second chunk."""
