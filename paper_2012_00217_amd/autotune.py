@@ -5,7 +5,9 @@ in the environment) take four launch parameters:
 bytes of a row chunk, bytes per lane, tiles per XCD group and workgroups per
 XCD.  Which combination is fastest depends on the sector dimension (how far the
 high-bond gathers reach compared with an XCD's L2 and the last-level cache) and
-on the row width of the block.  This tool times one block Jacobi-PCG call (the
+on the row width of the block, and little on the filling: the shapes are timed
+at half filling (with a schedule in the environment, which selects these
+kernels there) and serve sparse sectors of about the same dimension.  This tool times one block Jacobi-PCG call (the
 kernels that dominate a solve) for a staged set of candidates at each shape and
 writes the winners into ``csrc/apply_schedules.inc``, which the library compiles
 in.  Run it on the GPU, then rebuild:

@@ -595,7 +595,12 @@ struct Sched {
 };
 
 // Schedules measured best on the MI355X by the package's autotuner, keyed by
-// chain length, sector dimension, bytes per row of the block and element size.
+// chain length, sector dimension, bytes per row of the block and element size.  They
+// were tuned at half filling.  On sectors far from it, which run the gather kernels by
+// default, the nearest entry is never slower than the default schedule (CG step, L = 20 to
+// 32 with 5 to 7 up spins, n = 38,760 to 1,184,040, 16 to 128 columns): 128-byte rows of
+// FP32 0.69 to 0.81 of its time, 256- and 512-byte rows of n > 340,000 0.90 to 1.00, the
+// others equal.
 struct SchedEntry {
   int L;
   int64_t n;
@@ -1196,8 +1201,11 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
     if (H.col_ok && column_grid_fits(n, b)) {
       // One workgroup per column: every sector whose vector fits the LDS.  Per CG
       // step, against the best of the other two: 3.3 for 24 us (L = 12, 16 FP64
-      // columns), 5.7 for 28 (L = 14, 32 FP64), 14.8 for 30 (L = 16, 32 FP32); 32 for 33
-      // at its largest (L = 16, 32 FP64), where it takes 32 of the 256 CUs.
+      // columns), 5.7 for 28 (L = 14, 32 FP64), 14.8 for 30 (L = 16, 32 FP32).  FP64 of more
+      // than 7,168 rows keeps p and x in the L2 and is closest: n = 12,870, 1, 4, 16, 32,
+      // 64 and 256 columns 32.1, 32.2, 32.6, 32.9, 35.1 and 37.8 us, gather 38.9, 42.8,
+      // 45.3, 36.0, 46.1 and 185; n = 8,008 28.7, 28.8, 29.0, 29.2, 31.2 and 33.0 for 39.0,
+      // 43.4, 44.2, 32.0, 39.2 and 160.
       ColumnJob<T> job{&H, sigma, jac, R, ldr, W, ldw, b, m, keep, m_keep};
       if (t_cg_fuser && keep < 0 && tm == nullptr && stop == nullptr) {
         fuse_call(*t_cg_fuser, {-(int64_t)sizeof(T), b, m, n}, job, s,
