@@ -1220,11 +1220,13 @@ void run_pcg(const Ham& H, double sigma, const T* jac, const T* R, int64_t ldr, 
       return;
     }
     if (panel_usable<T>(H, b)) {
-      // (a fused batch too: panel calls have no joint form)
-      // Panels: measured no slower than the gather kernels at L = 17 to 24 for 1 to
-      // 128 columns of either type (us per step, panels for gathers: L = 17, 64
-      // FP64 columns 57 for 57; L = 18, 32 FP32 41 for 46; L = 20, 64 FP64 217 for 303;
-      // L = 21, 17 FP64 146 for 359; L = 24, 64 FP32 1,880 for 2,580).
+      // Panels (in a fused batch too: they have no joint form).  At L = 17 to 24 for 1 to
+      // 256 columns of either type no slower than the gather kernels at half filling (us
+      // per step, panels for gathers: L = 17, 64 FP64 columns 57 for 57; L = 18, 32 FP32 41
+      // for 46; L = 20, 64 FP64 217 for 303; L = 21, 17 FP64 146 for 359; L = 24, 64 FP32
+      // 1,880 for 2,580), and off it, to the mean rows of the rule, but for two of 180 shapes
+      // (16 steps: L = 18, 12 up, 64 FP64 1,059 for 1,016; L = 24, 15 up, 1 FP32 3,113 for
+      // 3,020).
       run_pcg_panel<T>(H, sigma, jac, R, ldr, W, ldw, b, m, s, tm, stop, keep, m_keep);
       return;
     }
